@@ -20,6 +20,7 @@
 #pragma once
 
 #include "common.cuh"
+#include "split3.cuh"
 
 namespace hmm {
 
@@ -181,6 +182,172 @@ __device__ __forceinline__ float coop_emit(const floatx4 &u, const float4 &b, fl
     x[3] = u[3] * b.w;
     const float part = ((x[0] + x[1]) + x[2]) + x[3];
     return sum_row_groups(part);
+}
+
+// ---- The same step on the bf16 matrix cores (split3.cuh).
+//
+// alpha~ is exchanged as its three bf16 pieces, written once by the wave that forms
+// it: piece p of sequence s is a row of NP values in chunks of 16 bytes, chunk
+// (c, g) holding the states 32 c + 4 g + 0..3 and 32 c + 16 + 4 g + 0..3, which is
+// the B operand of lane (s, g) for the K = 32 block c (one 16-byte LDS read).  Rows
+// are padded by 16 bytes, so that the 16 lanes of an LDS pass hit 16 bank groups.
+//
+// Two accumulators per output block: the products hi hi, and the five smaller ones,
+// added at the end, so that the small terms are not rounded into the large sum block
+// by block and two chains fill the matrix core's latency.
+template <int R>
+struct SplitShape {
+    static constexpr int NP = 16 * R;
+    static constexpr int ROW = NP * 2 + 16;      // bytes of one sequence's row of a piece
+    static constexpr int PIECE = TILE * ROW;
+    static constexpr int BUF = 3 * PIECE;        // one step's exchange
+    // shares of the per-sequence sum: one per group of GS blocks, rows of PSR floats
+    // (padded to 4, the padding zero) per sequence
+    static constexpr int GS = R > 8 ? 2 : 1;
+    static constexpr int NG = R / GS;
+    static constexpr int PSR = (NG + 3) / 4 * 4 + 4;
+    static constexpr int PS = TILE * PSR;
+};
+
+// Fragments of owned blocks r0 + b: slot j of a[b][c] is A[i][o] (A^T rows, forward) with
+// o = 16 (r0 + b) + sl and i = 32 c + 16 (j / 4) + 4 g + j % 4.
+template <int R, int BO>
+struct SplitFrags {
+    Split8 a[BO][R / 2];
+    __device__ __forceinline__ void load_fwd(const SplitConst &sc, const float *Ak, int N, int r0, int g, int sl) {
+        const int lane_off = opaque(4 * g * N + 16 * r0 + sl);
+#pragma unroll
+        for (int b = 0; b < BO; ++b)
+#pragma unroll
+            for (int c = 0; c < R / 2; ++c) {
+                float q[8];
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const int i0 = 32 * c + 16 * (j / 4) + j % 4;
+                    q[j] = (i0 + 4 * g < N && 16 * (r0 + b) + sl < N) ? Ak[lane_off + i0 * N + 16 * b] : 0.0f;
+                }
+                a[b][c] = split8(sc, q);
+                // Four blocks take the register file of a SIMD: 21 of the 32 fragments (252
+                // registers) are put into accumulation registers here, where the matrix
+                // instructions read them; left to itself the compiler copied 223 registers
+                // back on every step (forward of 256 states, 16384 sequences: 22.2 -> 19.9 ms).
+                if constexpr (BO == 4) {
+                    if (b * (R / 2) + c < 21) {
+#pragma unroll
+                        for (int p = 0; p < 3; ++p) {
+                            uintx4 w = __builtin_bit_cast(uintx4, a[b][c].p[p]);
+                            asm volatile("" : "+a"(w));
+                            a[b][c].p[p] = __builtin_bit_cast(bf16x8, w);
+                        }
+                    }
+                }
+            }
+    }
+};
+
+// Chunk (c, g) of sequence sl in every piece.
+template <int R>
+__device__ __forceinline__ void split_read(const unsigned char *buf, int c, int g, int sl, bf16x8 (&q)[3]) {
+    using SH = SplitShape<R>;
+#pragma unroll
+    for (int p = 0; p < 3; ++p) q[p] = *(const bf16x8 *)(buf + p * SH::PIECE + sl * SH::ROW + 64 * c + 16 * g);
+}
+
+// u[b] = (fragments . X) 2^-e, X from the exchange buffer; q0: its chunk 0, which a caller
+// may request before it forms e.  The operands of chunk c + 1 are read while chunk c's
+// products issue; the scheduling barriers keep the compiler from hoisting every read.
+template <int R, int BO>
+__device__ __forceinline__ void split_matvec(const SplitFrags<R, BO> &f, const unsigned char *buf, const bf16x8 (&q0)[3],
+                                             int e, int g, int sl, floatx4 (&u)[BO]) {
+    floatx4 lo[BO];
+#pragma unroll
+    for (int b = 0; b < BO; ++b) u[b] = lo[b] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+    bf16x8 qn[3] = {q0[0], q0[1], q0[2]};
+#pragma unroll
+    for (int c = 0; c < R / 2; ++c) {
+        const bf16x8 q[3] = {qn[0], qn[1], qn[2]};
+        if (c + 1 < R / 2) split_read<R>(buf, c + 1, g, sl, qn);
+#pragma unroll
+        for (int t = 0; t < SPLIT_TERMS; ++t)
+#pragma unroll
+            for (int b = 0; b < BO; ++b) {
+                floatx4 &acc = t == SPLIT_TERMS - 1 ? u[b] : lo[b];
+                acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(f.a[b][c].p[SPLIT_A[t]], q[SPLIT_X[t]], acc, 0, 0, 0);
+            }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int b = 0; b < BO; ++b)
+#pragma unroll
+        for (int v = 0; v < 4; ++v) u[b][v] = ldexp_f(u[b][v] + lo[b][v], -e);
+}
+
+// Own blocks r0 .. r0 + BO - 1 of sequence sl into the exchange buffer, split.
+template <int R, int BO>
+__device__ __forceinline__ void split_write(const SplitConst &sc, const float (&x)[BO][4], unsigned char *buf, int r0,
+                                            int g, int sl) {
+    using SH = SplitShape<R>;
+    unsigned char *row = buf + sl * SH::ROW + 64 * (r0 / 2) + 16 * g + 8 * (r0 & 1);
+    uint32_t w[3][BO][2];
+#pragma unroll
+    for (int b = 0; b < BO; ++b)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) split_pair(sc, x[b][2 * h], x[b][2 * h + 1], w[0][b][h], w[1][b][h], w[2][b][h]);
+#pragma unroll
+    for (int p = 0; p < 3; ++p) {
+        if constexpr (BO == 1) {
+            *(uint2 *)(row + p * SH::PIECE) = uint2{w[p][0][0], w[p][0][1]};
+        } else {
+#pragma unroll
+            for (int b = 0; b < BO; b += 2)
+                *(uint4 *)(row + p * SH::PIECE + 32 * b) = uint4{w[p][b][0], w[p][b][1], w[p][b + 1][0], w[p][b + 1][1]};
+        }
+    }
+}
+
+// The wave's shares of the per-sequence sum of x.
+template <int R, int BO>
+__device__ __forceinline__ void split_shares(const float (&x)[BO][4], float *psum, int r0, int g, int sl) {
+#pragma clang fp contract(off)
+    using SH = SplitShape<R>;
+#pragma unroll
+    for (int i = 0; i < BO; i += SH::GS) {
+        float part = x[i][0];
+#pragma unroll
+        for (int b = i; b < i + SH::GS; ++b)
+#pragma unroll
+            for (int v = (b == i ? 1 : 0); v < 4; ++v) part = part + x[b][v];
+        part = sum_row_groups(part);
+        psum[sl * SH::PSR + (r0 + i) / SH::GS] = part;  // the four lanes of a sequence write the same value
+    }
+}
+
+// alpha~ blocks x = u o b and the wave's shares of the per-sequence sum.
+template <int R, int BO>
+__device__ __forceinline__ void split_emit(const floatx4 (&u)[BO], const float4 (&b)[BO], float (&x)[BO][4], float *psum,
+                                           int r0, int g, int sl) {
+#pragma clang fp contract(off)
+#pragma unroll
+    for (int i = 0; i < BO; ++i) {
+        x[i][0] = u[i][0] * b[i].x;
+        x[i][1] = u[i][1] * b[i].y;
+        x[i][2] = u[i][2] * b[i].z;
+        x[i][3] = u[i][3] * b[i].w;
+    }
+    split_shares<R, BO>(x, psum, r0, g, sl);
+}
+
+// Per-sequence sum of the previous step from the shares (fixed order).
+template <int R>
+__device__ __forceinline__ float split_step_sum(const float *psum, int sl) {
+    using SH = SplitShape<R>;
+    float cs = 0.0f;
+#pragma unroll
+    for (int i = 0; i < SH::NG; i += 4) {
+        const float4 q = *(const float4 *)&psum[sl * SH::PSR + i];
+        cs = (((cs + q.x) + q.y) + q.z) + q.w;
+    }
+    return cs;
 }
 
 }  // namespace hmm

@@ -5,9 +5,15 @@
 // per action evaluated independently, Sec. 3 item 3), distributed over a
 // workgroup of R / BO waves (R = NP / 16 state blocks, BO blocks per wave) per
 // tile of 16 length-sorted sequences of one model (see coop_step.cuh for the
-// data movement).  Per step and workgroup: 4 R^2 MFMAs of 16x16x4 FP32, one
-// barrier, one exchange of 16 x NP floats through LDS.  Emission rows B^T[o][.] come from L2 (B^T of one model is up to
-// 1 MiB and stays resident in its XCD's L2); the symbol and row of step t+1
+// data movement).  Per step and workgroup: 3 R^2 bf16 MFMAs of 16x16x32 (FP32 products
+// by three-way splits, split3.cuh; the gradient's variant keeps 4 R^2 MFMAs of 16x16x4
+// FP32), one barrier, one exchange of the tile's alpha through LDS.  Bound by the power
+// the matrix cores draw: with 256 states the clock falls to 2.1 GHz and the products run
+// at 1.4 PFLOP/s of bf16, and interleaving the epilogue with them (which filled the idle
+// vector slots) changed nothing.  16 models of 256 states, 16384 sequences of 256-4096
+// steps: 38.5 ms in FP32, 20.0 ms split; 5 models of 100 states, 1001 sequences against
+// all: 0.861 -> 0.544 ms.  Emission rows B^T[o][.] come from L2 (B^T of one model is up
+// to 1 MiB and stays resident in its XCD's L2); the symbol and row of step t+1
 // are fetched during step t.  The gradient's variant (CKPT) keeps alphahat for
 // the backward pass: every step's row and exponent when the workspace's rows
 // hold the batch (decided on the device from the row prefix), else a
@@ -26,9 +32,13 @@ constexpr int CCH = 32;  // symbols per staging chunk
 template <int R, int BO, bool CKPT>
 __global__ void __launch_bounds__(R / BO * WAVE) k_fwd_coop(DevPtrs d, FwdLaunch f) {
     using SH = CoopShape<R>;
+    using SP = SplitShape<R>;
+    constexpr bool SPLIT = !CKPT;
     constexpr int NP = SH::NP;
     constexpr int XROW = SH::XROW;
-    __shared__ __align__(16) float xch[SH::floats];
+    __shared__ __align__(16) float xch[SPLIT ? 1 : SH::floats];
+    __shared__ __align__(16) unsigned char xsp[2][SPLIT ? SP::BUF : 16];  // alpha~ in pieces
+    __shared__ __align__(16) float psp[2][SPLIT ? SP::PS : 4];            // shares of the sums
     __shared__ int32_t sym[2][CCH * TILE];
     __shared__ int32_t tile_sh;
     const int lane = threadIdx.x & (WAVE - 1);
@@ -44,6 +54,10 @@ __global__ void __launch_bounds__(R / BO * WAVE) k_fwd_coop(DevPtrs d, FwdLaunch
     const int G = gridDim.x;
     const int k_first = G >= K ? (int)(blockIdx.x % K) : (int)blockIdx.x;
     const int k_step = G >= K ? K : G;
+    const SplitConst sc;
+    if (SPLIT) {
+        for (int i = threadIdx.x; i < 2 * SP::PS; i += blockDim.x) psp[0][i] = 0.0f;  // the padding stays zero
+    }
     for (int k = k_first; k < K; k += k_step) {
         const int grp = f.all_pairs ? 0 : k;
         const int gbeg = f.gstart[grp], gend = f.gstart[grp + 1];
@@ -52,7 +66,11 @@ __global__ void __launch_bounds__(R / BO * WAVE) k_fwd_coop(DevPtrs d, FwdLaunch
         const float *btk = f.bt + (size_t)k * M * NP;
         const float *pik = d.pi + (size_t)k * N;
         float af[BO][R][4];
-        coop_load_fwd_fragments<R, BO>(af, d.A + (size_t)k * N * N, N, r0, g, sl);
+        SplitFrags<R, BO> sf;
+        if constexpr (SPLIT)
+            sf.load_fwd(sc, d.A + (size_t)k * N * N, N, r0, g, sl);
+        else
+            coop_load_fwd_fragments<R, BO>(af, d.A + (size_t)k * N * N, N, r0, g, sl);
 
         for (;;) {
             if (threadIdx.x == 0) tile_sh = atomicAdd(&f.queue[k], 1);
@@ -130,7 +148,8 @@ __global__ void __launch_bounds__(R / BO * WAVE) k_fwd_coop(DevPtrs d, FwdLaunch
             auto read_phase = [&](int t) -> int {
                 int e = 0;
                 if (t > 0) {
-                    const float cs = coop_step_sum<R>(psum + ((t - 1) & 1) * R * TILE, sl);
+                    const float cs = SPLIT ? split_step_sum<R>(psp[(t - 1) & 1], sl)
+                                           : coop_step_sum<R>(psum + ((t - 1) & 1) * R * TILE, sl);
                     e = frexp_exp(cs);
                     if (t - 1 == T - 1) {
                         E_end = E;
@@ -183,19 +202,29 @@ __global__ void __launch_bounds__(R / BO * WAVE) k_fwd_coop(DevPtrs d, FwdLaunch
             // has passed; the barrier of step 32 c + 1 publishes it long before
             // its first reader, step 32 c + 30.  Loading and storing inside one
             // iteration keeps the staging registers out of the loop latch.
-            auto step = [&](int t, const float4 (&bcur)[BO], float4 (&bnext)[BO], int o1, int &o2, bool chunk_ld,
+            // With four blocks per wave (the whole register file of a SIMD) there is one set:
+            // the rows of step t are requested at its start with its own symbol (o1), and
+            // the product, some 3000 cycles, covers them; o2 is then the symbol of step t + 1.
+            constexpr int AHEAD = BO == 4 ? 0 : 1;
+            auto step = [&](int t, float4 (&bcur)[BO], float4 (&bnext)[BO], int o1, int &o2, bool chunk_ld,
                             bool chunk_st) {
                 int on = o1;
-                symbad |= (t + 1 < T) && (on < 0 || on >= M);
+                symbad |= (t + AHEAD < T) && (on < 0 || on >= M);
                 on = ((unsigned)on < (unsigned)M) ? on : 0;
 #pragma unroll
-                for (int b = 0; b < BO; ++b) bnext[b] = *(const float4 *)&btk[(size_t)on * NP + 16 * (r0 + b) + 4 * g];
+                for (int b = 0; b < BO; ++b) (AHEAD ? bnext[b] : bcur[b]) = *(const float4 *)&btk[(size_t)on * NP + 16 * (r0 + b) + 4 * g];
                 // first operand of this step's product, requested with the block sums
                 const float *xprev = xbuf + ((t - 1) & 1) * TILE * XROW;
-                const float4 q0 = *(const float4 *)&xprev[sl * XROW + 4 * g];
+                const unsigned char *sprev = xsp[(t - 1) & 1];
+                float4 q0;
+                bf16x8 s0[3];
+                if constexpr (SPLIT)
+                    split_read<R>(sprev, 0, g, sl, s0);
+                else
+                    q0 = *(const float4 *)&xprev[sl * XROW + 4 * g];
                 const int e = read_phase(t);
                 if (chunk_ld) load_chunk(t + CCH);
-                o2 = read_sym(t + 2);
+                o2 = read_sym(t + 1 + AHEAD);
                 floatx4 u[BO];
                 if (t == 0) {
 #pragma unroll
@@ -206,28 +235,41 @@ __global__ void __launch_bounds__(R / BO * WAVE) k_fwd_coop(DevPtrs d, FwdLaunch
                             u[b][v] = i < N ? pik[i] : 0.0f;
                         }
                 } else {
-                    coop_matvec_q0<R, BO>(af, xprev, q0, e, g, sl, u);
+                    if constexpr (SPLIT)
+                        split_matvec<R, BO>(sf, sprev, s0, e, g, sl, u);
+                    else
+                        coop_matvec_q0<R, BO>(af, xprev, q0, e, g, sl, u);
                 }
+                if constexpr (SPLIT) {
+                    split_emit<R, BO>(u, bcur, x, psp[t & 1], r0, g, sl);
+                    split_write<R, BO>(sc, x, xsp[t & 1], r0, g, sl);
+                } else {
 #pragma unroll
-                for (int b = 0; b < BO; ++b) {
-                    const float part = coop_emit(u[b], bcur[b], x[b]);
-                    *(float4 *)&xbuf[(t & 1) * TILE * XROW + sl * XROW + 16 * (r0 + b) + 4 * g] =
-                        float4{x[b][0], x[b][1], x[b][2], x[b][3]};
-                    if (g == 0) psum[(t & 1) * R * TILE + (r0 + b) * TILE + sl] = part;
+                    for (int b = 0; b < BO; ++b) {
+                        const float part = coop_emit(u[b], bcur[b], x[b]);
+                        *(float4 *)&xbuf[(t & 1) * TILE * XROW + sl * XROW + 16 * (r0 + b) + 4 * g] =
+                            float4{x[b][0], x[b][1], x[b][2], x[b][3]};
+                        if (g == 0) psum[(t & 1) * R * TILE + (r0 + b) * TILE + sl] = part;
+                    }
                 }
                 if (chunk_st) store_chunk(t / CCH + 1);
                 // the waves exchange alphahat through LDS only: the emission rows and
                 // symbols requested for the next steps stay in flight across the barrier
                 lds_barrier();
             };
-            int oA = 0, oB = read_sym(1);  // symbols of the next even and odd steps
+            int oA = AHEAD ? 0 : o, oB = AHEAD ? read_sym(1) : 0;  // symbols of the next even and odd steps
             int t = 0;
             for (; t + 1 < Tmax; t += 2) {
                 const bool chunk = w == 0 && t > 0 && (t % CCH) == 0;
-                step(t, bA, bB, oB, oA, chunk, false);
-                step(t + 1, bB, bA, oA, oB, false, chunk);
+                if constexpr (AHEAD) {
+                    step(t, bA, bB, oB, oA, chunk, false);
+                    step(t + 1, bB, bA, oA, oB, false, chunk);
+                } else {
+                    step(t, bA, bA, oA, oB, chunk, false);
+                    step(t + 1, bA, bA, oB, oA, false, chunk);
+                }
             }
-            if (t < Tmax) step(t++, bA, bB, oB, oA, false, false);
+            if (t < Tmax) step(t++, bA, AHEAD ? bB : bA, AHEAD ? oB : oA, AHEAD ? oA : oB, false, false);
             read_phase(t);
             if (has && g == 0 && w == 0) {
                 float r = (float)((double)E_end * LN2 + (double)logf(c_end));
@@ -242,13 +284,15 @@ __global__ void __launch_bounds__(R / BO * WAVE) k_fwd_coop(DevPtrs d, FwdLaunch
 }
 
 // Blocks per wave: one up to 8 blocks (N <= 128), two above, so that a lane's
-// fragments (4 R BO floats) fit the register budget of the workgroup size.
-template <int R>
-constexpr int coop_bo() { return R > 8 ? 2 : 1; }
+// fragments (6 R BO registers in pieces) fit the register budget of the workgroup size;
+// four at 256 states (384 of the 512 registers of a lane that has its SIMD to itself: with
+// two blocks in eight waves the fragments alone take 192 of 256).
+template <int R, bool CKPT>
+constexpr int coop_bo() { return R == 16 && !CKPT ? 4 : R > 8 ? 2 : 1; }
 
 template <int R, bool CKPT>
 hipError_t launch_t(const DevPtrs &d, const FwdLaunch &f, int cu_count, hipStream_t st) {
-    constexpr int BO = coop_bo<R>();
+    constexpr int BO = coop_bo<R, CKPT>();
     auto kern = k_fwd_coop<R, BO, CKPT>;
     int per_cu = 0;
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, R / BO * WAVE, 0);
