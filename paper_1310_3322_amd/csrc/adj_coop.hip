@@ -49,7 +49,10 @@ namespace {
 
 constexpr int SSEG = 64;     // steps of symbols staged at a time (a whole segment up to T = 4096)
 constexpr int PACH = 16;     // symbols per staging chunk of the pipelined kernel (its LDS is full)
-constexpr int STREAM_D = 3;  // blocks of streamed fragments in flight
+// Blocks of streamed fragments in flight: four, three at 256 states, whose count
+// accumulators leave fewer registers (gradient of 16 models x 16384 sequences of 256
+// states: 138.8 ms with four, 134.8 with three; 200 states, 3000 sequences: 11.2 and 11.5).
+constexpr int stream_d(int R) { return R == 16 ? 3 : 4; }
 
 // Blocks per wave: as in the forward (one up to 8 blocks, two above).
 constexpr int adj_bo(int R) { return R > 8 ? 2 : 1; }
@@ -81,7 +84,7 @@ struct AdjFrags;
 template <int R, int BO>
 struct AdjFrags<R, BO, false> {
     float af[BO][R][4], ab[BO][R][4];
-    __device__ __forceinline__ void load(const float *Ak, int N, int r0, int g, int sl, const float4 *, int) {
+    __device__ __forceinline__ void load(const float *Ak, int N, int r0, int g, int sl, const float4 *) {
         coop_load_fwd_fragments<R, BO>(af, Ak, N, r0, g, sl);
         coop_load_bwd_fragments<R, BO>(ab, Ak, N, r0, g, sl);
     }
@@ -96,17 +99,19 @@ struct AdjFrags<R, BO, false> {
 template <int R, int BO>
 struct AdjFrags<R, BO, true> {
     const float4 *faf, *fab;
-    // frag_k: model k's two sets; lane_w: offset of this wave's and lane's first float4
-    __device__ __forceinline__ void load(const float *, int, int, int, int, const float4 *frag_k, int lane_w) {
-        constexpr size_t set = (size_t)R * R * WAVE;  // float4 per set (NW waves x R blocks x 64 lanes x BO)
-        faf = frag_k + lane_w;
-        fab = frag_k + set + lane_w;
+    CoopStream<R, BO, stream_d(R)> st;
+    // frag_w: this wave's fragments of model k's first set; the second follows a set later
+    __device__ __forceinline__ void load(const float *, int, int, int, int, const float4 *frag_w) {
+        faf = frag_w;
+        fab = frag_w + (size_t)R * R * WAVE;
     }
-    __device__ __forceinline__ void fwd(const float *x, float4 q0, int e, int g, int sl, floatx4 (&u)[BO]) const {
-        coop_matvec_stream_q0<R, BO, STREAM_D>(faf, x, q0, e, g, sl, u);
+    __device__ __forceinline__ void prime_fwd(int lane) { st.prime(faf, lane); }
+    __device__ __forceinline__ void prime_bwd(int lane) { st.prime(fab, lane); }
+    __device__ __forceinline__ void fwd(const float *x, float4 q0, int e, int g, int sl, floatx4 (&u)[BO]) {
+        st.matvec(x, q0, e, 16 * g + sl, u);
     }
-    __device__ __forceinline__ void bwd(const float *x, int g, int sl, floatx4 (&u)[BO]) const {
-        coop_matvec_stream<R, BO, STREAM_D>(fab, x, 0, g, sl, u);
+    __device__ __forceinline__ void bwd(const float *x, int g, int sl, floatx4 (&u)[BO]) {
+        st.matvec(x, *(const float4 *)&x[sl * CoopShape<R>::XROW + 4 * g], 0, 16 * g + sl, u);
     }
 };
 
@@ -122,10 +127,18 @@ __global__ void __launch_bounds__(R / BO * WAVE) k_adj_coop(DevPtrs d, AdjLaunch
     constexpr int NW = SH::NW;
     constexpr int XROW = SH::XROW;
     extern __shared__ __align__(16) unsigned char smem[];
-    __shared__ __align__(16) float xch[SH::xch_floats];
+    __shared__ __align__(16) float xch[FULL ? 4 : SH::xch_floats];
     __shared__ __align__(16) float wex[SH::w_floats];
     __shared__ float atile_all[SH::at_floats];
-    __shared__ int32_t symseg[SSEG * TILE];
+    // LATE: the walk over the stored rows with streamed fragments requests the row of step
+    // t - 1 after the product of step t, and reads symbols and exponents from LDS.  Loads
+    // return in order, so the row, requested from memory at the start of the step, held up
+    // every fragment streamed after it by its latency (16 models of 256 states, 16384
+    // sequences: walk 96.6 ms, 83.9 ms this way).  With
+    // resident fragments the early request is 1 % faster.
+    constexpr bool LATE = FULL && STREAM;
+    __shared__ int32_t symseg[FULL && !LATE ? 1 : SSEG * TILE];
+    __shared__ int32_t expseg[LATE ? SSEG * TILE : 1];
     __shared__ int32_t tile_sh;
     float *nbl = (float *)smem;  // [M][NP] emission-count partial when NBLDS
     // [2][ceil(M / 2)] words after the partial: slot masks of the symbols of a step
@@ -169,8 +182,7 @@ __global__ void __launch_bounds__(R / BO * WAVE) k_adj_coop(DevPtrs d, AdjLaunch
         const float *Ak = d.A + (size_t)k * N * N;
         if (ntiles > 0) {
             AdjFrags<R, BO, STREAM> fr;
-            fr.load(Ak, N, r0, g, sl, STREAM ? (const float4 *)a.frag + (size_t)k * 2 * R * R * WAVE : nullptr,
-                    (w * R * WAVE + lane) * BO);
+            fr.load(Ak, N, r0, g, sl, STREAM ? (const float4 *)a.frag + ((size_t)k * 2 * R + r0) * R * WAVE : nullptr);
             floatx4 C[BO][R];  // rows 16 (r0 + b) + 4 g + v, columns 16 rj + sl; per tile
 
             for (;;) {
@@ -230,6 +242,26 @@ __global__ void __launch_bounds__(R / BO * WAVE) k_adj_coop(DevPtrs d, AdjLaunch
                     et = a.aexp[row];
                     const int o = sbase[min(t, tlim)];
                     ot = ((unsigned)o < (unsigned)M) ? o : 0;
+                };
+                auto load_rows = [&](int t, float4 (&aq)[BO]) {
+                    int64_t row = T > 0 ? rb + min(max(t, 0), T - 1) : 0;
+                    if (!dbg_in(row, a.grad_rows, HMM_DEBUG_GRAD_ROWS)) row = 0;
+#pragma unroll
+                    for (int b = 0; b < BO; ++b) aq[b] = *(const float4 *)&a.arow[(size_t)row * NP + 16 * (r0 + b) + 4 * g];
+                };
+                // symbols and exponents of the SSEG steps t, t - 1, .. by every wave (one load
+                // round trip for all of them)
+                auto stage_steps = [&](int t) {
+                    __syncthreads();
+                    for (int s = w * 4 + g; s < SSEG; s += NW * 4) {
+                        const int ts = max(t - s, 0);
+                        const int o = sbase[min(ts, tlim)];
+                        symseg[s * TILE + sl] = ((unsigned)o < (unsigned)M) ? o : 0;
+                        int64_t row = T > 0 ? rb + min(ts, T - 1) : 0;
+                        if (!dbg_in(row, a.grad_rows, HMM_DEBUG_GRAD_ROWS)) row = 0;
+                        expseg[s * TILE + sl] = a.aexp[row];
+                    }
+                    __syncthreads();
                 };
                 // gamma_1 of this lane's states, added to n_pi after the tile (a global atomic
                 // inside the step would make every step wait for all outstanding loads)
@@ -350,6 +382,7 @@ __global__ void __launch_bounds__(R / BO * WAVE) k_adj_coop(DevPtrs d, AdjLaunch
 #pragma unroll
                             for (int b = 0; b < BO; ++b) bb[b] = *(const float4 *)&btk[(size_t)o * NP + 16 * (r0 + b) + 4 * g];
                             floatx4 u[BO];
+                            if constexpr (STREAM) fr.prime_fwd(lane);
                             // the checkpoint row enters unscaled (exponent 0), later rows by 2^-e
                             fr.fwd(xprev, q0, (t == t0 + 1) ? 0 : e, g, sl, u);
 #pragma unroll
@@ -366,7 +399,10 @@ __global__ void __launch_bounds__(R / BO * WAVE) k_adj_coop(DevPtrs d, AdjLaunch
                     // are requested during step t, and the emission row of step t at its start
                     float4 aq_n[BO];
                     int et_n = 0, ot_n = 0;
-                    if constexpr (FULL) {
+                    if constexpr (STREAM) fr.prime_bwd(lane);
+                    if constexpr (LATE) {
+                        load_rows(t1 - 1, aq_n);
+                    } else if constexpr (FULL) {
                         fetch_full(t1 - 1, aq_n, et_n, ot_n);
                     } else {
 #pragma unroll
@@ -377,19 +413,30 @@ __global__ void __launch_bounds__(R / BO * WAVE) k_adj_coop(DevPtrs d, AdjLaunch
                     for (int t = t1 - 1; t >= t0; --t) {
                         const int tl = t - t0;
                         float al[BO][4];
+                        auto take_al = [&]() {
 #pragma unroll
-                        for (int b = 0; b < BO; ++b) {
-                            al[b][0] = aq_n[b].x;
-                            al[b][1] = aq_n[b].y;
-                            al[b][2] = aq_n[b].z;
-                            al[b][3] = aq_n[b].w;
+                            for (int b = 0; b < BO; ++b) {
+                                al[b][0] = aq_n[b].x;
+                                al[b][1] = aq_n[b].y;
+                                al[b][2] = aq_n[b].z;
+                                al[b][3] = aq_n[b].w;
+                            }
+                        };
+                        int et, ot;
+                        if constexpr (LATE) {
+                            const int s = (t1 - 1 - t) % SSEG;
+                            if (s == 0) stage_steps(t);
+                            ot = symseg[s * TILE + sl];
+                            et = expseg[s * TILE + sl];
+                        } else {
+                            take_al();
+                            et = et_n;
+                            ot = ot_n;
                         }
-                        const int et = et_n;
-                        const int ot = ot_n;
                         float4 bb[BO];
 #pragma unroll
                         for (int b = 0; b < BO; ++b) bb[b] = *(const float4 *)&btk[(size_t)ot * NP + 16 * (r0 + b) + 4 * g];
-                        {
+                        if constexpr (!LATE) {
                             // unconditional (index clamped at the segment start), so that the
                             // wait for the emission row above can leave these loads in flight
                             const int tp = tl > 0 ? tl - 1 : 0;
@@ -427,6 +474,7 @@ __global__ void __launch_bounds__(R / BO * WAVE) k_adj_coop(DevPtrs d, AdjLaunch
 #pragma unroll
                                 for (int v = 0; v < 4; ++v) be[b][v] = inv;
                         }
+                        if constexpr (LATE) take_al();
                         if (!DEFER && live) {
                             // emission counts before the C update, whose MFMAs cover the
                             // atomics' latency before the next step's first load is awaited.
@@ -477,6 +525,7 @@ __global__ void __launch_bounds__(R / BO * WAVE) k_adj_coop(DevPtrs d, AdjLaunch
 #pragma unroll
                                 for (int v = 0; v < 4; ++v)
                                     atile[(b * TILE + sl) * 17 + 4 * g + v] = trans ? wgt * al[b][v] : 0.0f;
+                            if constexpr (LATE) load_rows(t - 1, aq_n);
                             wave_lds_sync();
                             if (DEFER) {
                                 // all operands of the C update first; the deferred emission
@@ -521,6 +570,8 @@ __global__ void __launch_bounds__(R / BO * WAVE) k_adj_coop(DevPtrs d, AdjLaunch
                             wave_lds_sync();
                         } else if (DEFER) {
                             flush_pending();
+                        } else if (LATE) {
+                            load_rows(t - 1, aq_n);
                         }
                         if (DEFER) {
                             // this step's emission counts wait in registers for the next step,
@@ -547,6 +598,7 @@ __global__ void __launch_bounds__(R / BO * WAVE) k_adj_coop(DevPtrs d, AdjLaunch
                         // w_t = b_t o betahat_t 2^-e_t; zero where the sequence has ended or
                         // takes no part (its values may be inf / NaN and w enters the
                         // contraction over sequences of C)
+                        if constexpr (STREAM) fr.prime_bwd(lane);  // the next step's first fragments
 #pragma unroll
                         for (int b = 0; b < BO; ++b) {
                             const float wn0 = live ? ldexp_f(bb[b].x * be[b][0], -et) : 0.0f;
@@ -671,7 +723,7 @@ __global__ void __launch_bounds__(2 * R * WAVE) k_adj_pipe(DevPtrs d, AdjLaunch 
         const float *Ak = d.A + (size_t)k * N * N;
         if (ntiles > 0) {
             AdjFrags<R, 1, false> fr;
-            fr.load(Ak, N, w, g, sl, nullptr, 0);
+            fr.load(Ak, N, w, g, sl, nullptr);
             // each group adds half of the transition counts: rows 16 w + 4 g + v,
             // columns 16 (rj0 + rj) + sl, rj0 = 0 (backward group) or R / 2; per tile
             constexpr int RH = R / 2;
@@ -1216,7 +1268,7 @@ __global__ void __launch_bounds__(256) k_grows_reduce(AdjLaunch a) {
 }
 
 // Streamed fragments of model k: set 0 (A_k^T, recompute) and set 1 (A_k,
-// beta), float4 index (((set * NW + w) * R + rp) * 64 + lane) * BO + b with
+// beta), float4 index (((set * NW + w) * R + rp) * BO + b) * 64 + lane with
 // components v = 0..3:
 //   set 0: A_k[16 rp + 4 g + v][16 (BO w + b) + sl],  set 1: A_k[16 (BO w + b) + sl][16 rp + 4 g + v]
 // (g = lane / 16, sl = lane % 16; zero outside N x N).
@@ -1226,8 +1278,8 @@ __global__ void k_coop_frags(const float *A, float4 *frag, int N, int R, int BO)
     const size_t idx = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (idx >= per_model) return;
     const int NW = R / BO;
-    const int b = (int)(idx % BO);
-    const int lane = (int)((idx / BO) % WAVE);
+    const int lane = (int)(idx % WAVE);
+    const int b = (int)((idx / WAVE) % BO);
     const int rp = (int)((idx / ((size_t)BO * WAVE)) % R);
     const int w = (int)((idx / ((size_t)BO * WAVE * R)) % NW);
     const int set = (int)(idx / ((size_t)BO * WAVE * R * NW));

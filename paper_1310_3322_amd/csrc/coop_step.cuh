@@ -118,59 +118,59 @@ __device__ __forceinline__ void coop_matvec(const float (&f)[BO][R][4], const fl
     coop_matvec_q0<R, BO>(f, xrow_base, q0, e, g, sl, u);
 }
 
-// Fragments streamed from memory instead of registers, for state counts whose
-// fragments and count accumulators do not fit the register file together.
-// fr points at this lane's fragments of block rp = 0 of the wave, laid out
-// [R rp][64 lanes][BO] float4 (v = 0..3 in the float4); the fragments of block
-// rp + D are loaded while the MFMAs of block rp issue (each load's offset is
-// opaque, so that its address is formed next to it rather than hoisted out of
-// the step loop as one register pair per block).  Same chains and order as
-// coop_matvec, so the results are bit-identical to it.
+// Fragments streamed from memory instead of registers, for state counts whose fragments
+// and count accumulators do not fit the register file together: a wave's are [R blocks
+// rp][BO][64 lanes] float4 (v = 0..3 in the float4), one scalar pointer runs through
+// them with the loads of a block at immediate offsets (one offset register per load
+// would live across the step loop), and D blocks are in flight.  Loads return in order,
+// so whatever a kernel requests from memory before a product delays its fragments by that
+// request's latency; prime() requests the first D blocks and may be placed ahead of
+// the barrier that publishes X.  Same chains and order as coop_matvec, so the results are
+// bit-identical to it.
 template <int R, int BO, int D>
-__device__ __forceinline__ void coop_matvec_stream_q0(const float4 *fr, const float *xrow_base, float4 q0, int e, int g,
-                                                      int sl, floatx4 (&u)[BO]) {
+struct CoopStream {
+    typedef const __attribute__((address_space(1))) char *gptr;  // (a generic pointer makes the loads flat)
+    gptr next;
+    floatx4 ring[D][BO];
+    __device__ __forceinline__ void fetch(floatx4 (&f)[BO], int lane) {
+        const uint32_t l16 = (uint32_t)lane * 16u;
+        asm volatile("" : "+s"(next));
 #pragma unroll
-    for (int b = 0; b < BO; ++b) u[b] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-    const float *row = xrow_base + sl * CoopShape<R>::XROW + 4 * g;
-    float4 ring[D][BO];
-#pragma unroll
-    for (int dd = 0; dd < D; ++dd)
-#pragma unroll
-        for (int b = 0; b < BO; ++b) ring[dd][b] = fr[opaque(dd * WAVE * BO + b)];
-    float4 qn = q0;
-#pragma unroll
-    for (int rp = 0; rp < R; ++rp) {
-        const float4 q = qn;
-        if (rp + 1 < R) qn = *(const float4 *)&row[16 * (rp + 1)];
-        float4 f[BO];
-#pragma unroll
-        for (int b = 0; b < BO; ++b) f[b] = ring[rp % D][b];
-        if (rp + D < R) {
-#pragma unroll
-            for (int b = 0; b < BO; ++b) ring[rp % D][b] = fr[opaque((rp + D) * WAVE * BO + b)];
-        }
-        const float in[4] = {q.x, q.y, q.z, q.w};
-#pragma unroll
-        for (int v = 0; v < 4; ++v)
-#pragma unroll
-            for (int b = 0; b < BO; ++b) {
-                const float a = v == 0 ? f[b].x : v == 1 ? f[b].y : v == 2 ? f[b].z : f[b].w;
-                u[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, in[v], u[b], 0, 0, 0);
-            }
-        __builtin_amdgcn_sched_barrier(0);
+        for (int b = 0; b < BO; ++b)
+            f[b] = *(const __attribute__((address_space(1))) floatx4 *)(next + l16 + b * (WAVE * 16));
+        next += BO * WAVE * 16;
     }
+    __device__ __forceinline__ void prime(const float4 *fr, int lane) {
+        const uint64_t p = (uint64_t)fr;  // wave-uniform
+        const uint32_t lo = __builtin_amdgcn_readfirstlane((int)(uint32_t)p), hi = __builtin_amdgcn_readfirstlane((int)(p >> 32));
+        next = (gptr)(((uint64_t)hi << 32) | lo);
 #pragma unroll
-    for (int b = 0; b < BO; ++b)
+        for (int dd = 0; dd < D; ++dd) fetch(ring[dd], lane);
+    }
+    // after prime(); q0 as in coop_matvec_q0
+    __device__ __forceinline__ void matvec(const float *xrow_base, float4 q0, int e, int lane, floatx4 (&u)[BO]) {
+        const float *row = xrow_base + (lane & 15) * CoopShape<R>::XROW + 4 * (lane >> 4);
 #pragma unroll
-        for (int v = 0; v < 4; ++v) u[b][v] = ldexp_f(u[b][v], -e);
-}
-
-template <int R, int BO, int D>
-__device__ __forceinline__ void coop_matvec_stream(const float4 *fr, const float *xrow_base, int e, int g, int sl,
-                                                   floatx4 (&u)[BO]) {
-    const float4 q0 = *(const float4 *)&xrow_base[sl * CoopShape<R>::XROW + 4 * g];
-    coop_matvec_stream_q0<R, BO, D>(fr, xrow_base, q0, e, g, sl, u);
-}
+        for (int b = 0; b < BO; ++b) u[b] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+        float4 qn = q0;
+#pragma unroll
+        for (int rp = 0; rp < R; ++rp) {
+            const float in[4] = {qn.x, qn.y, qn.z, qn.w};
+            if (rp + 1 < R) qn = *(const float4 *)&row[16 * (rp + 1)];
+#pragma unroll
+            for (int v = 0; v < 4; ++v)
+#pragma unroll
+                for (int b = 0; b < BO; ++b)
+                    u[b] = __builtin_amdgcn_mfma_f32_16x16x4f32(ring[rp % D][b][v], in[v], u[b], 0, 0, 0);
+            if (rp + D < R) fetch(ring[rp % D], lane);
+            __builtin_amdgcn_sched_barrier(0);
+        }
+#pragma unroll
+        for (int b = 0; b < BO; ++b)
+#pragma unroll
+            for (int v = 0; v < 4; ++v) u[b][v] = ldexp_f(u[b][v], -e);
+    }
+};
 
 // alpha~ block = u o b, its share of the per-sequence sum (identical in the 4
 // lanes of a sequence).
