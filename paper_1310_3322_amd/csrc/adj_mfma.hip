@@ -13,25 +13,40 @@
 // ln A and ln B.
 //
 // Memory: the forward kernel stored alphahat every L = ceil(sqrt(Tmax)) steps
-// (Tmax the longest sequence of the 16-sequence tile).  Walking the segments
-// last to first, the wave recomputes alphahat for the L steps of a segment
-// with the forward kernel's own step code (bit-identical), parks them in a
-// per-wave buffer in global memory, and runs the backward recursion through
-// the segment.  Memory per sequence grows with sqrt(T).
+// (Tmax the longest sequence of the 16-sequence tile).  The segments of L steps are
+// taken last to first: alphahat is recomputed from the checkpoint with the forward
+// kernel's own step code (bit-identical) into a segment buffer in global memory, which the
+// backward recursion then walks.  Memory per sequence grows with sqrt(T).
 //
-// Per step and tile of 16 sequences (layout as in the forward kernel):
-//   betahat_t = A w_{t+1}            16x16x4 MFMAs, A fragments in registers
-//   C += X^T W                       X = w_s alphahat_t, W = w_{t+1}: transposed
-//                                    through a per-wave LDS tile so the 16
-//                                    sequences become the MFMA contraction axis
-//   n_B^T[o_t][i] += w_s gamma_t(i)  into the wave's LDS partial (slots that share
-//                                    a symbol add in slot-rank rounds), written to
-//                                    the tile's slab slot after each tile; or, when
-//                                    the partial does not fit, to the global counts
+// A tile of 16 sequences is a chain of dependent steps, so the work of a step is split
+// over the four waves of a workgroup, one per SIMD, by what depends on what:
+//   REC     recomputes segment j - 1 while the others are on segment j
+//   WALK    betahat_t = A w_{t+1}, w_t = b_t o betahat_t 2^-e_t   (the chain itself)
+//   XI      C += X^T W, X = w_s alphahat_t, W = w_{t+1}: transposed through LDS so
+//           that the 16 sequences become the MFMA contraction axis
+//   COUNTS  n_B^T[o_t][i] += w_s gamma_t(i) into the LDS partial of the workgroup
+//           (slots that share a symbol add in slot-rank rounds), written to the tile's
+//           slab slot after each tile; or, when the partial does not fit, to the global
+//           counts; n_pi
+// WALK leaves w_{t+1} and betahat_t of CS steps in one half of an LDS ring; XI and
+// COUNTS take them CS steps later from the other half, so the waves meet at one barrier
+// every CS steps (and REC's segment at one every L).  Symbols are requested two chunks
+// of CS steps ahead, emission rows and alphahat one chunk ahead.
+//
+// Bound by the latency of a step of WALK and REC (about the same: four dependent 16x16x4
+// MFMAs of 33 cycles and some 20 dependent vector instructions at 16 states) while the
+// tiles are few, by the matrix and vector instructions of the four parts once they fill
+// the card.  An FP32 MFMA leaves no issue slot to its own wave's vector instructions, which
+// is why the parts of a step gain from having a SIMD each.  Against one wave per tile that
+// does all of it in turn, with every operand requested when needed, the backward pass of
+// 4096 sequences of 50-400 (12 models, 16 states, 64 symbols) went from 455 to 142 us, that of
+// 147 sequences of 20-200 (5 states) from 286 to 66 us (0.33 us a step), and that of 65536
+// sequences of 16-2048 (64 models, 32 states, 256 symbols) from 5.1 to 3.2 ms.
 //
 // Global counts are 64-bit fixed-point sums (common.cuh) and each tile's sums are
 // formed in an order fixed by its data, so the counts do not depend on which
-// wave takes which tile.
+// workgroup takes which tile.
+#include <algorithm>
 #include <climits>
 
 #include "common.cuh"
@@ -41,24 +56,25 @@
 namespace hmm {
 namespace {
 
-constexpr int ADJ_CH = 16;                  // symbols per staging chunk in the recompute
-constexpr int ADJ_SYM_STRIDE = ADJ_CH + 1;
+// Lower slots of the tile that hold the lane's symbol o and add to its table, among the
+// slots s, s - tables, .. that share it.  Two to eight tables: the 16 lanes of a DPP row
+// hold the tile's slots, and row_shr brings the symbol n slots below (-1 from outside).
+template <int SHIFT>
+__device__ __forceinline__ int same_below(int o) {
+    return __builtin_amdgcn_update_dpp(-1, o, 0x110 + SHIFT, 0xf, 0xf, false) == o ? 1 : 0;
+}
+__device__ __forceinline__ int shared_rank(int o, int ntab) {
+    int n = same_below<8>(o);
+    if (ntab <= 4) n += same_below<4>(o) + same_below<12>(o);
+    if (ntab == 2) n += same_below<2>(o) + same_below<6>(o) + same_below<10>(o) + same_below<14>(o);
+    return n;
+}
 
+// Emission counts of a step into an LDS partial (its table of the lane's slot at nbl):
+// the lane's 4 consecutive states of each 16-state block at (16 r + 4 g) ^ (4 o & swz) of
+// symbol o's row, in rounds of the slot rank of the lane's symbol.
 template <int R>
-struct AdjShape {
-    static constexpr int NP = 16 * R;
-    static constexpr int XS = NP + 4;       // padded row of the transposition tiles
-    static constexpr int tile_floats = 2 * TILE * XS;               // X and W
-    static constexpr int sym_ints = 2 * TILE * ADJ_SYM_STRIDE;
-    static constexpr int per_wave_bytes = tile_floats * 4 + sym_ints * 4;
-};
-
-// Emission counts of a step into the LDS partial: the lane's 4 consecutive states
-// of each 16-state block at (16 r + 4 g) ^ (4 o & swz) of symbol o's row, in rounds
-// of the slot rank of the lane's symbol.
-template <int R>
-__device__ __forceinline__ void partial_add(float *nbl, int ot, int swz, int g, bool live, int rank,
-                                            const float (&gm)[R][4]) {
+__device__ __forceinline__ void partial_add(float *nbl, int ot, int swz, int g, int rank, const float (&gm)[R][4]) {
     constexpr int NP = 16 * R;
     auto rmw = [&]() {
 #pragma unroll
@@ -72,41 +88,59 @@ __device__ __forceinline__ void partial_add(float *nbl, int ot, int swz, int g, 
             *(float4 *)q = x;
         }
     };
-    if (live && rank == 0) rmw();
-    for (int rr = 1; __ballot(live && rank >= rr) != 0; ++rr) {
+    if (rank == 0) rmw();
+    for (int rr = 1; __ballot(rank >= rr) != 0; ++rr) {
         wave_lds_sync();
-        if (live && rank == rr) rmw();
+        if (rank == rr) rmw();
     }
 }
 
 __host__ __device__ inline int nb_swizzle_mask(int NP) { return (NP & (NP - 1)) == 0 ? NP - 4 : 0; }
 
-template <int R, int WAVES, bool NBLDS>
-__global__ void __launch_bounds__(WAVES * WAVE) k_adj_mfma(DevPtrs d, AdjLaunch a) {
-    static_assert(!NBLDS || WAVES == 1, "the LDS partial holds one tile's counts");
-    using SH = AdjShape<R>;
-    constexpr int NP = SH::NP;
-    constexpr int XS = SH::XS;
+enum Role { REC, WALK, XI, COUNTS, ROLES };
+
+template <int R, int CS>
+struct AdjShape {
+    static constexpr int NP = 16 * R;
+    static constexpr int XS = NP + 4;       // padded row of the transposition tiles
+    static constexpr int static_bytes = 2 * CS * (TILE * XS * 4 + R * WAVE * 16) + TILE * XS * 4 + TILE * 4 +
+                                        2 * CS * TILE * 4 + 64;
+    // segment buffer: two halves (segment parity) of alphahat [L][R][64] float4 and
+    // packed exponents [L][64]
+    static constexpr int seg_step = WAVE * (4 * R + 1);  // floats per step
+};
+
+// Waves per SIMD that the registers are kept to.
+constexpr int adj_waves(int R, int CS) { return CS == 4 ? 2 : R == 1 ? 4 : R == 2 ? 3 : 2; }
+
+template <int R, bool NBLDS, int CS>
+__global__ void __launch_bounds__(ROLES * WAVE) __attribute__((amdgpu_waves_per_eu(adj_waves(R, CS), 8)))
+k_adj_tile(DevPtrs d, AdjLaunch a) {
+    using SH = AdjShape<R, CS>;
+    constexpr int NP = SH::NP, XS = SH::XS;
     extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ __align__(16) float wring[2][CS][TILE * XS];     // w_{t+1} of the sequences that go on
+    __shared__ __align__(16) float4 bring[2][CS][R][WAVE];      // betahat_t
+    __shared__ __align__(16) float xt[TILE * XS];
+    __shared__ float mlast[TILE];                               // m_T of each sequence
+    __shared__ int32_t elast[2][CS][TILE];                      // exponents of a segment's last steps
+    __shared__ int32_t tile_sh;
     const int lane = threadIdx.x & (WAVE - 1);
-    const int wave = threadIdx.x / WAVE;
+    const int role = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
     const int sl = lane & 15, g = lane >> 4;
     const int K = a.K, N = a.N, M = a.M;
     const int swz = nb_swizzle_mask(NP);
     const int F = fixed_exponent(*a.wmax, a.S, a.max_len);
-    float *nbl = (float *)smem;                                        // [M][NP] when NBLDS
-    uint32_t *ranktab = (uint32_t *)(smem + (NBLDS ? (size_t)M * NP * 4 : 0));  // [M] slot masks when NBLDS
-    unsigned char *wbase = smem + (NBLDS ? (size_t)M * NP * 4 + (size_t)M * 4 : 0) + (size_t)wave * SH::per_wave_bytes;
-    float *xt = (float *)wbase;                                        // [16][XS]
-    float *wt = xt + TILE * XS;                                        // [16][XS]
-    int32_t *sym = (int32_t *)(wt + TILE * XS);                        // [2][16][ADJ_SYM_STRIDE]
+    float *nbl = (float *)smem;  // [tables][M + 1][NP] when NBLDS
+    const int ntab = a.ntab, tab = (M + 1) * NP;
+    uint32_t *ranktab = (uint32_t *)(nbl + tab);  // [m2] slot masks of slot_rank when there is one table
+    const int m2 = (M + 1) / 2;
 
-    const int slot = blockIdx.x * WAVES + wave;
-    float *segf = a.seg + (size_t)slot * a.seg_stride;
-    const int Lcap = (int)(a.seg_stride / (WAVE * (4 * R + 2)));
-    float4 *seg_alpha = (float4 *)segf;                                // [Lcap][R][64]
-    int32_t *seg_e = (int32_t *)(segf + (size_t)Lcap * WAVE * 4 * R);  // [Lcap][64]
-    int32_t *seg_o = seg_e + (size_t)Lcap * WAVE;                      // [Lcap][64]
+    float *segf = a.seg + (size_t)blockIdx.x * a.seg_stride;
+    const int64_t half = a.seg_stride / 2;
+    const int Lcap = (int)(half / SH::seg_step);
+    auto seg_alpha = [&](int j) { return (float4 *)(segf + (j & 1) * half); };
+    auto seg_e = [&](int j) { return (int32_t *)(segf + (j & 1) * half + (size_t)Lcap * WAVE * 4 * R); };
 
     const int G = gridDim.x;
     const int k_first = G >= K ? (int)(blockIdx.x % K) : (int)blockIdx.x;
@@ -114,240 +148,315 @@ __global__ void __launch_bounds__(WAVES * WAVE) k_adj_mfma(DevPtrs d, AdjLaunch 
     for (int k = k_first; k < K; k += k_step) {
         const int gbeg = a.gstart[k], gend = a.gstart[k + 1];
         const int ntiles = (gend - gbeg + TILE - 1) / TILE;
+        if (ntiles == 0) continue;
         const float *btk = a.bt + (size_t)k * M * NP;
         unsigned long long *B64k = a.B64 + (size_t)k * M * NP;  // [M][NP] symbol-major global counts
         if (NBLDS) {
-            for (int i = lane; i < M * NP; i += WAVE) nbl[i] = 0.0f;
-            for (int i = lane; i < M; i += WAVE) ranktab[i] = 0u;
-            wave_lds_sync();
+            __syncthreads();
+            for (int i = threadIdx.x; i < ntab * tab; i += ROLES * WAVE) nbl[i] = 0.0f;
+            if (ntab == 1)
+                for (int i = threadIdx.x; i < m2; i += ROLES * WAVE) ranktab[i] = 0u;
         }
-        if (ntiles > 0) {
-            const float *Ak = d.A + (size_t)k * N * N;
-            float af[R][R][4], ab[R][R][4];
-            load_fwd_fragments<R>(af, Ak, N, g, sl);
-            load_bwd_fragments<R>(ab, Ak, N, g, sl);
-            floatx4 C[R][R];  // per tile
+        const float *Ak = d.A + (size_t)k * N * N;
+        float fr[R][R][4];  // fragments of A^T (REC) or A (WALK)
+        if (role == REC) load_fwd_fragments<R>(fr, Ak, N, g, sl);
+        if (role == WALK) load_bwd_fragments<R>(fr, Ak, N, g, sl);
 
-            for (;;) {
-                const int tile = wave_pop(&a.queue[k]);
-                if (tile >= ntiles) break;
+        for (;;) {
+            __syncthreads();
+            if (threadIdx.x == 0) tile_sh = atomicAdd(&a.queue[k], 1);
+            __syncthreads();
+            const int tile = __builtin_amdgcn_readfirstlane(tile_sh);  // scalar exit: the loop holds barriers
+            if (tile >= ntiles) break;
 
-                const int pos = gbeg + tile * TILE + sl;
-                const bool has = pos < gend;
-                const int seq = has ? a.perm[pos] : 0;
-                int32_t T = 0;
-                int64_t off = 0;
-                bool act = false;
-                if (has) {
-                    T = d.lengths[seq];
-                    off = d.offsets[seq];
-                    const int mk = d.model_of_seq[seq];
-                    const bool bad = seq_bad(T, off, a.max_len, a.total) || mk < 0 || mk >= K;
-                    if (bad) T = 0;
-                    act = !bad && T > 0 && a.flag[pos] == 0;
-                }
-                // the checkpoint grid uses the forward kernel's tile maximum
-                const int Tmax = wave_max_int(T);
-                if (Tmax > 0) {
-#pragma unroll
-                for (int ri = 0; ri < R; ++ri)
-#pragma unroll
-                    for (int rj = 0; rj < R; ++rj) C[ri][rj] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
-                bool lane_nan = false;
+            const int pos = gbeg + tile * TILE + sl;
+            const bool has = pos < gend;
+            const int seq = has ? a.perm[pos] : 0;
+            int32_t T = 0;
+            int64_t off = 0;
+            bool act = false;
+            if (has) {
+                T = d.lengths[seq];
+                off = d.offsets[seq];
+                const int mk = d.model_of_seq[seq];
+                const bool bad = seq_bad(T, off, a.max_len, a.total) || mk < 0 || mk >= K;
+                if (bad) T = 0;
+                act = !bad && T > 0 && a.flag[pos] == 0;
+            }
+            // the checkpoint grid uses the forward kernel's tile maximum
+            const int Tmax = __builtin_amdgcn_readfirstlane(wave_max_int(T));
+            if (Tmax > 0) {
                 int L = 1;
                 while (L * L < Tmax) ++L;
                 if (!dbg_in(L - 1, Lcap, HMM_DEBUG_SEGMENT)) return;  // segment buffer too short (debug build)
                 const int nseg = (Tmax + L - 1) / L;
+                const int nch = (L + CS - 1) / CS;  // chunks per segment
                 const float wgt = act ? (a.weight ? a.weight[seq] : 1.0f) : 0.0f;
-                const int st_slot = lane >> 2, st_part = lane & 3;
-                const int32_t st_T = __shfl(T, st_slot, WAVE);
-                const int64_t st_off = __shfl(off, st_slot, WAVE);
-                const int32_t *st_src = d.symbols + st_off;
-                auto stage = [&](int buf, int t0) {
-                    int32_t *dst = sym + buf * TILE * ADJ_SYM_STRIDE + st_slot * ADJ_SYM_STRIDE + st_part * (ADJ_CH / 4);
-#pragma unroll
-                    for (int u = 0; u < ADJ_CH / 4; ++u) {
-                        const int p = t0 + st_part * (ADJ_CH / 4) + u;
-                        int o = p < st_T ? st_src[p] : 0;
-                        dst[u] = ((unsigned)o < (unsigned)M) ? o : 0;
+                const int32_t *sbase = T > 0 ? d.symbols + off : d.symbols;
+                const int tlim = T > 0 ? T - 1 : 0;
+                auto seg_len = [&](int j) { return min(L, Tmax - j * L); };
+                auto load_sym = [&](int t) { return sbase[min(max(t, 0), tlim)]; };
+                auto checked = [&](int o) { return ((unsigned)o < (unsigned)M) ? o : 0; };
+                // A chunk of backward steps: t0, t0 - 1, .. (n of them, none or less than none where
+                // the segment is shorter or there is no segment)
+                struct Chunk {
+                    int t0, n;
+                };
+                auto back_chunk = [&](int j, int s) {
+                    const int n = j >= 0 && j < nseg ? seg_len(j) - s * CS : 0;
+                    return Chunk{j * L + n - 1, n};
+                };
+                // the chunk `by` (1 or 2) after chunk s of segment j
+                auto back_after = [&](int j, int s, int by) {
+                    for (int i = 0; i < by; ++i) {
+                        const bool wrap = s + 1 == nch;
+                        j -= wrap ? 1 : 0;
+                        s = wrap ? 0 : s + 1;
                     }
+                    return back_chunk(j, s);
                 };
 
-                float wn[R][4];      // w_{t+1}
-#pragma unroll
-                for (int r = 0; r < R; ++r)
-#pragma unroll
-                    for (int v = 0; v < 4; ++v) wn[r][v] = 0.0f;
-
-                for (int j = nseg - 1; j >= 0; --j) {
-                    const int t0 = j * L;
-                    const int t1 = min(t0 + L, Tmax);
-                    // ---- recompute alphahat over [t0, t1) from checkpoint j
-                    float acur[R][4];
-                    int e0 = 0;
-                    if (t0 < T) {
-                        const float *src = a.ckpt + ((size_t)pos * a.nck + j) * NP;
-#pragma unroll
-                        for (int r = 0; r < R; ++r) {
-                            float4 q = *(const float4 *)&src[16 * r + 4 * g];
-                            acur[r][0] = q.x;
-                            acur[r][1] = q.y;
-                            acur[r][2] = q.z;
-                            acur[r][3] = q.w;
+                if (role == REC) {
+                    // segment nseg - 1 - p in phase p; first step of the chunk `by` after chunk s of
+                    // segment j
+                    auto rec_after = [&](int j, int s, int by) {
+                        for (int i = 0; i < by; ++i) {
+                            const bool wrap = s + 1 == nch;
+                            j -= wrap ? 1 : 0;
+                            s = wrap ? 0 : s + 1;
                         }
-                        e0 = a.ckexp[(size_t)pos * a.nck + j];
-                    } else {
+                        return max(j, 0) * L + s * CS;
+                    };
+                    float4 bc[CS][R], bn[CS][R];
+                    int oc[CS], on[CS], o2[CS];
+                    float4 ckn[R] = {};  // checkpoint of the next phase's segment
+                    int cken = 0;
+                    auto load_ckpt = [&](int j) {
+                        if (j >= 0 && j * L < T) {
+                            const float *src = a.ckpt + ((size_t)pos * a.nck + j) * NP;
 #pragma unroll
-                        for (int r = 0; r < R; ++r)
+                            for (int r = 0; r < R; ++r) ckn[r] = *(const float4 *)&src[16 * r + 4 * g];
+                            cken = a.ckexp[(size_t)pos * a.nck + j];
+                        } else {
 #pragma unroll
-                            for (int v = 0; v < 4; ++v) acur[r][v] = 0.0f;
+                            for (int r = 0; r < R; ++r) ckn[r] = float4{0.0f, 0.0f, 0.0f, 0.0f};
+                            cken = 0;
+                        }
+                    };
+                    load_ckpt(nseg - 1);
+#pragma unroll
+                    for (int u = 0; u < CS; ++u) {
+                        oc[u] = checked(load_sym(rec_after(nseg - 1, 0, 0) + u));
+                        on[u] = load_sym(rec_after(nseg - 1, 0, 1) + u);
+                        gather_b<R>(&btk[(size_t)oc[u] * NP], g, bc[u]);
                     }
-                    stage(0, t0);
-                    stage(1, t0 + ADJ_CH);
-                    wave_lds_sync();
+                    float acur[R][4];
+                    for (int p = 0; p <= nseg; ++p) {
+                        const int j = nseg - 1 - p;
+                        const int LB = j >= 0 ? seg_len(j) : 0;
+                        float4 *sa = seg_alpha(j);
+                        int32_t *se = seg_e(j);
+                        __syncthreads();  // the segment recomputed in the phase before is visible
+                        for (int s = 0; s < nch; ++s) {
+                            const int t2 = rec_after(j, s, 2);
+#pragma unroll
+                            for (int u = 0; u < CS; ++u) {
+                                on[u] = checked(on[u]);
+                                gather_b<R>(&btk[(size_t)on[u] * NP], g, bn[u]);
+                                o2[u] = load_sym(t2 + u);
+                            }
+#pragma unroll
+                            for (int u = 0; u < CS; ++u) {
+                                const int tl = s * CS + u;
+                                if (tl < LB) {
+                                    const int t = j * L + tl;
+                                    int e;
+                                    if (tl == 0) {
+#pragma unroll
+                                        for (int r = 0; r < R; ++r) {
+                                            acur[r][0] = ckn[r].x;
+                                            acur[r][1] = ckn[r].y;
+                                            acur[r][2] = ckn[r].z;
+                                            acur[r][3] = ckn[r].w;
+                                        }
+                                        e = cken;
+                                        load_ckpt(j - 1);
+                                    } else {
+                                        floatx4 uu[R];
+                                        tile_matvec<R>(fr, acur, uu);
+                                        emit_and_rescale<R>(uu, bc[u], acur, e);
+                                    }
+#pragma unroll
+                                    for (int r = 0; r < R; ++r)
+                                        sa[(size_t)(tl * R + r) * WAVE + lane] =
+                                            float4{acur[r][0], acur[r][1], acur[r][2], acur[r][3]};
+                                    se[(size_t)tl * WAVE + lane] = e;
+                                    if (LB - 1 - tl < CS && g == 0) elast[j & 1][LB - 1 - tl][sl] = e;
+                                    if (__ballot(t == T - 1) != 0) {  // m_T of the sequences that end here
+                                        float part = 0.0f;
+#pragma unroll
+                                        for (int r = 0; r < R; ++r)
+#pragma unroll
+                                            for (int v = 0; v < 4; ++v) part += acur[r][v];
+                                        const float m = sum_row_groups(part);
+                                        if (t == T - 1) mlast[sl] = m;
+                                    }
+                                }
+                            }
+#pragma unroll
+                            for (int u = 0; u < CS; ++u) {
+                                oc[u] = on[u];
+                                on[u] = o2[u];
+#pragma unroll
+                                for (int r = 0; r < R; ++r) bc[u][r] = bn[u][r];
+                            }
+                            lds_barrier();
+                        }
+                    }
+                } else if (role == WALK) {
+                    float wn[R][4];  // w_{t+1}
 #pragma unroll
                     for (int r = 0; r < R; ++r)
-                        seg_alpha[(size_t)(0 * R + r) * WAVE + lane] = float4{acur[r][0], acur[r][1], acur[r][2], acur[r][3]};
-                    seg_e[lane] = e0;
-                    seg_o[lane] = sym[sl * ADJ_SYM_STRIDE];
-                    for (int t = t0 + 1; t < t1; ++t) {
-                        const int tl = t - t0;
-                        if ((tl % ADJ_CH) == 0 && tl > 0) {
-                            // chunk tl / ADJ_CH is staged; refill the buffer of the one before
-                            stage(((tl / ADJ_CH) + 1) & 1, t + ADJ_CH);
-                            wave_lds_sync();
-                        }
-                        const int o = sym[((tl / ADJ_CH) & 1) * TILE * ADJ_SYM_STRIDE + sl * ADJ_SYM_STRIDE + (tl % ADJ_CH)];
-                        float4 b[R];
-                        gather_b<R>(&btk[(size_t)o * NP], g, b);
-                        floatx4 u[R];
-                        tile_matvec<R>(af, acur, u);
-                        int e;
-                        emit_and_rescale<R>(u, b, acur, e);
 #pragma unroll
-                        for (int r = 0; r < R; ++r)
-                            seg_alpha[(size_t)(tl * R + r) * WAVE + lane] =
-                                float4{acur[r][0], acur[r][1], acur[r][2], acur[r][3]};
-                        seg_e[(size_t)tl * WAVE + lane] = e;
-                        seg_o[(size_t)tl * WAVE + lane] = o;
+                        for (int v = 0; v < 4; ++v) wn[r][v] = 0.0f;
+                    float4 bc[CS][R], bn[CS][R];
+                    int on[CS], o2[CS], ec[CS], en[CS];
+#pragma unroll
+                    for (int u = 0; u < CS; ++u) {
+                        gather_b<R>(&btk[(size_t)checked(load_sym(back_chunk(nseg, 0).t0 - u)) * NP], g, bc[u]);
+                        on[u] = load_sym(back_after(nseg, 0, 1).t0 - u);
+                        ec[u] = 0;
                     }
-                    // ---- backward through the segment
-                    for (int t = t1 - 1; t >= t0; --t) {
-                        const int tl = t - t0;
-                        float al[R][4];
+                    int half_ring = 0;
+                    for (int p = 0; p <= nseg; ++p) {
+                        const int j = nseg - p;
+                        const int LA = p > 0 ? seg_len(j) : 0;
+                        const int32_t *se = seg_e(j);
+                        lds_barrier();  // (REC's barrier publishes the segment)
 #pragma unroll
-                        for (int r = 0; r < R; ++r) {
-                            float4 q = seg_alpha[(size_t)(tl * R + r) * WAVE + lane];
-                            al[r][0] = q.x;
-                            al[r][1] = q.y;
-                            al[r][2] = q.z;
-                            al[r][3] = q.w;
+                        for (int u = 0; u < CS; ++u) ec[u] = elast[j & 1][u][sl];
+                        for (int s = 0; s < nch; ++s, half_ring ^= 1) {
+                            const int t2 = back_after(j, s, 2).t0;
+#pragma unroll
+                            for (int u = 0; u < CS; ++u) {
+                                gather_b<R>(&btk[(size_t)checked(on[u]) * NP], g, bn[u]);
+                                o2[u] = load_sym(t2 - u);
+                                const int tn = LA - 1 - ((s + 1) * CS + u);
+                                en[u] = se[(size_t)max(tn, 0) * WAVE + lane];
+                            }
+#pragma unroll
+                            for (int u = 0; u < CS; ++u) {
+                                const int tl = LA - 1 - (s * CS + u);
+                                if (tl >= 0) {
+                                    const int t = j * L + tl;
+                                    float *wt = wring[half_ring][u];
+#pragma unroll
+                                    for (int r = 0; r < R; ++r)
+                                        *(float4 *)&wt[sl * XS + 16 * r + 4 * g] =
+                                            float4{wn[r][0], wn[r][1], wn[r][2], wn[r][3]};
+                                    floatx4 be[R];
+                                    tile_matvec<R>(fr, wn, be);
+                                    if (__ballot(t == T - 1) != 0) {
+                                        const float inv = 1.0f / mlast[sl];
+#pragma unroll
+                                        for (int r = 0; r < R; ++r)
+#pragma unroll
+                                            for (int v = 0; v < 4; ++v) be[r][v] = t == T - 1 ? inv : be[r][v];
+                                    }
+#pragma unroll
+                                    for (int r = 0; r < R; ++r)
+                                        bring[half_ring][u][r][lane] = float4{be[r][0], be[r][1], be[r][2], be[r][3]};
+                                    // w_t = b_t o betahat_t 2^-e_t; zero where the sequence has ended or
+                                    // takes no part (its values may be inf / NaN)
+                                    const bool live = act && t < T;
+#pragma unroll
+                                    for (int r = 0; r < R; ++r) {
+                                        wn[r][0] = live ? ldexp_f(bc[u][r].x * be[r][0], -ec[u]) : 0.0f;
+                                        wn[r][1] = live ? ldexp_f(bc[u][r].y * be[r][1], -ec[u]) : 0.0f;
+                                        wn[r][2] = live ? ldexp_f(bc[u][r].z * be[r][2], -ec[u]) : 0.0f;
+                                        wn[r][3] = live ? ldexp_f(bc[u][r].w * be[r][3], -ec[u]) : 0.0f;
+                                    }
+                                }
+                            }
+#pragma unroll
+                            for (int u = 0; u < CS; ++u) {
+                                on[u] = o2[u];
+                                ec[u] = en[u];
+#pragma unroll
+                                for (int r = 0; r < R; ++r) bc[u][r] = bn[u][r];
+                            }
+                            lds_barrier();
                         }
-                        const int et = seg_e[(size_t)tl * WAVE + lane];
-                        const int ot = seg_o[(size_t)tl * WAVE + lane];
-                        float part = 0.0f;
+                    }
+                } else if (role == XI) {
+                    // at the slot of a chunk, request its alphahat and take the chunk before
+                    floatx4 C[R][R];
 #pragma unroll
-                        for (int r = 0; r < R; ++r)
+                    for (int ri = 0; ri < R; ++ri)
 #pragma unroll
-                            for (int v = 0; v < 4; ++v) part += al[r][v];
-                        const float m = sum_row_groups(part);
-                        const bool live = act && t < T;          // gamma_t exists
-                        const bool trans = act && t + 1 < T;     // xi_t exists
-                        float be[R][4];
-                        if (t + 1 < Tmax) {
-                            floatx4 u[R];
-                            tile_matvec<R>(ab, wn, u);
+                        for (int rj = 0; rj < R; ++rj) C[ri][rj] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+                    float4 ac[CS][R], an[CS][R];
+                    // C += X^T W with X = w_s alphahat_t, W = w_{t+1}, the chunk's operands first
+                    auto take = [&](const Chunk &c, int hr) {
+                        float xa[CS][4][R], wb[CS][4][R];
+#pragma unroll
+                        for (int u = 0; u < CS; ++u) {
+                            const bool trans = act && u < c.n && c.t0 - u + 1 < T;
 #pragma unroll
                             for (int r = 0; r < R; ++r)
-#pragma unroll
-                                for (int v = 0; v < 4; ++v) be[r][v] = u[r][v];
-                            // C += X^T W with X = w_s alphahat_t, W = w_{t+1}
-#pragma unroll
-                            for (int r = 0; r < R; ++r) {
-                                float4 xv = trans ? float4{wgt * al[r][0], wgt * al[r][1], wgt * al[r][2], wgt * al[r][3]}
-                                                  : float4{0.0f, 0.0f, 0.0f, 0.0f};
-                                float4 wv = trans ? float4{wn[r][0], wn[r][1], wn[r][2], wn[r][3]}
-                                                  : float4{0.0f, 0.0f, 0.0f, 0.0f};
-                                *(float4 *)&xt[sl * XS + 16 * r + 4 * g] = xv;
-                                *(float4 *)&wt[sl * XS + 16 * r + 4 * g] = wv;
-                            }
+                                *(float4 *)&xt[sl * XS + 16 * r + 4 * g] =
+                                    float4{trans ? wgt * ac[u][r].x : 0.0f, trans ? wgt * ac[u][r].y : 0.0f,
+                                           trans ? wgt * ac[u][r].z : 0.0f, trans ? wgt * ac[u][r].w : 0.0f};
                             wave_lds_sync();
 #pragma unroll
-                            for (int q = 0; q < 4; ++q) {
-                                float xa[R], wb[R];
+                            for (int q = 0; q < 4; ++q)
 #pragma unroll
                                 for (int r = 0; r < R; ++r) {
-                                    xa[r] = xt[(4 * q + g) * XS + 16 * r + sl];
-                                    wb[r] = wt[(4 * q + g) * XS + 16 * r + sl];
+                                    xa[u][q][r] = xt[(4 * q + g) * XS + 16 * r + sl];
+                                    wb[u][q][r] = wring[hr][u][(4 * q + g) * XS + 16 * r + sl];
                                 }
+                            wave_lds_sync();
+                        }
+#pragma unroll
+                        for (int u = 0; u < CS; ++u) {
+                            if (u >= c.n) continue;  // (its ring entry holds an older step)
+#pragma unroll
+                            for (int q = 0; q < 4; ++q)
 #pragma unroll
                                 for (int ri = 0; ri < R; ++ri)
 #pragma unroll
                                     for (int rj = 0; rj < R; ++rj)
-                                        C[ri][rj] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[ri], wb[rj], C[ri][rj], 0, 0, 0);
-                            }
-                            wave_lds_sync();
-                        } else {
-#pragma unroll
-                            for (int r = 0; r < R; ++r)
-#pragma unroll
-                                for (int v = 0; v < 4; ++v) be[r][v] = 0.0f;
+                                        C[ri][rj] =
+                                            __builtin_amdgcn_mfma_f32_16x16x4f32(xa[u][q][ri], wb[u][q][rj], C[ri][rj], 0, 0, 0);
                         }
-                        if (t == T - 1) {
-                            const float inv = 1.0f / m;
+                    };
+                    Chunk cp{0, 0};
+                    int half_ring = 0;
+                    for (int p = 0; p <= nseg; ++p) {
+                        const int j = nseg - p;
+                        const float4 *sa = seg_alpha(j);
+                        lds_barrier();
+                        for (int s = 0; s < nch; ++s, half_ring ^= 1) {
+                            const Chunk cn = back_chunk(j, s);
 #pragma unroll
-                            for (int r = 0; r < R; ++r)
-#pragma unroll
-                                for (int v = 0; v < 4; ++v) be[r][v] = inv;
-                        }
-                        // gamma_t -> emission counts (and initial counts at t = 0)
-                        {
-                            float gm[R][4];
-#pragma unroll
-                            for (int r = 0; r < R; ++r)
-#pragma unroll
-                                for (int v = 0; v < 4; ++v) {
-                                    const int i = 16 * r + 4 * g + v;
-                                    gm[r][v] = (live && i < N) ? wgt * al[r][v] * be[r][v] : 0.0f;
-                                    lane_nan |= !__builtin_isfinite(gm[r][v]);
-                                }
-                            if (NBLDS) {
-                                partial_add<R>(nbl, ot, swz, g, live, slot_rank(ranktab, ot, sl), gm);
-                            } else if (live) {
+                            for (int u = 0; u < CS; ++u)
 #pragma unroll
                                 for (int r = 0; r < R; ++r)
+                                    an[u][r] = sa[(size_t)(max(cn.n - 1 - u, 0) * R + r) * WAVE + lane];
+                            if (cp.n > 0) take(cp, half_ring ^ 1);
+                            // (the copies wait for this chunk's loads, which thus end before REC writes
+                            // the other half again)
 #pragma unroll
-                                    for (int v = 0; v < 4; ++v) {
-                                        const int i = 16 * r + 4 * g + v;
-                                        const float x = __builtin_isfinite(gm[r][v]) ? gm[r][v] : 0.0f;
-                                        if (i < N) atomicAdd(&B64k[(size_t)ot * NP + quad_t(i)], to_fixed(x, F));
-                                    }
-                            }
-                            if (live && t == 0) {
+                            for (int u = 0; u < CS; ++u)
 #pragma unroll
-                                for (int r = 0; r < R; ++r)
-#pragma unroll
-                                    for (int v = 0; v < 4; ++v) {
-                                        const int i = 16 * r + 4 * g + v;
-                                        if (i < N) add_fixed(&a.pi64[(size_t)k * N + i], gm[r][v], F, &a.nanflag[k]);
-                                    }
-                            }
-                        }
-                        // w_t = b_t o betahat_t 2^-e_t for the step before
-                        float4 b[R];
-                        gather_b<R>(&btk[(size_t)ot * NP], g, b);
-#pragma unroll
-                        for (int r = 0; r < R; ++r) {
-                            wn[r][0] = ldexp_f(b[r].x * be[r][0], -et);
-                            wn[r][1] = ldexp_f(b[r].y * be[r][1], -et);
-                            wn[r][2] = ldexp_f(b[r].z * be[r][2], -et);
-                            wn[r][3] = ldexp_f(b[r].w * be[r][3], -et);
+                                for (int r = 0; r < R; ++r) ac[u][r] = an[u][r];
+                            cp = cn;
+                            lds_barrier();
                         }
                     }
-                }
-                // this tile's n_A = A o C (row base opaque: the flush's addresses are formed
-                // here, not kept live across the tile loop)
-                {
+                    if (cp.n > 0) take(cp, half_ring ^ 1);
+                    // this tile's n_A = A o C (row base opaque: the flush's addresses are formed
+                    // here, not kept live across the tile loop)
                     const int rb = opaque(k * N + 4 * g);
 #pragma unroll
                     for (int ri = 0; ri < R; ++ri)
@@ -359,112 +468,263 @@ __global__ void __launch_bounds__(WAVES * WAVE) k_adj_mfma(DevPtrs d, AdjLaunch 
                                 const size_t e = (size_t)(rb + 16 * ri + v) * N + jj;
                                 if (i < N && jj < N) add_fixed(&a.A64[e], d.A[e] * C[ri][rj][v], F, &a.nanflag[k]);
                             }
-                }
-                if (lane_nan) atomicOr(&a.nanflag[k], 1);
-                }  // Tmax > 0
-                if (NBLDS) {
-                    // the tile's emission partial into its slab slot (zeros for an empty tile)
-                    wave_lds_sync();
-                    const int64_t slot = slab_slot(gbeg, k, tile);
-                    float *dst = a.slab + (size_t)(dbg_in(slot, slab_slots(a.S, a.K), HMM_DEBUG_SLAB) ? slot : 0) * M * NP;
-                    for (int idx = lane; idx < M * NP; idx += WAVE) {
-                        const int o = idx / NP, ic = idx % NP;
-                        dst[(size_t)o * NP + (ic ^ (o * 4 & swz))] = nbl[idx];
-                        nbl[idx] = 0.0f;
+                } else {
+                    // COUNTS, likewise one chunk behind
+                    float nan_acc = 0.0f;  // NaN once a gamma was not finite
+                    int states = 0;        // bit 4 r + v: the lane's state 16 r + 4 g + v is below N
+#pragma unroll
+                    for (int q = 0; q < 4 * R; ++q) states |= (16 * (q / 4) + 4 * g + q % 4 < N ? 1 : 0) << q;
+                    float4 ac[CS][R], an[CS][R];
+                    int oc[CS], on[CS];
+#pragma unroll
+                    for (int u = 0; u < CS; ++u) oc[u] = 0;
+                    // gamma_t = alphahat_t o betahat_t of the chunk's steps, then their counts (steps and
+                    // sequences that are not live add zero)
+                    auto take = [&](const Chunk &c, int hr) {
+                        float gm[CS][R][4];
+#pragma unroll
+                        for (int u = 0; u < CS; ++u) {
+                            const uint32_t live = act && u < c.n && c.t0 - u < T ? ~0u : 0u;
+#pragma unroll
+                            for (int r = 0; r < R; ++r) {
+                                const float4 be = bring[hr][u][r][lane];
+                                const float4 al = ac[u][r];
+                                const float x[4] = {wgt * al.x * be.x, wgt * al.y * be.y, wgt * al.z * be.z, wgt * al.w * be.w};
+#pragma unroll
+                                for (int v = 0; v < 4; ++v) {
+                                    const uint32_t keep = live & (uint32_t)__builtin_amdgcn_sbfe(states, 4 * r + v, 1);
+                                    gm[u][r][v] = __uint_as_float(__float_as_uint(x[v]) & keep);
+                                    nan_acc = fmaf(gm[u][r][v], 0.0f, nan_acc);
+                                }
+                            }
+                        }
+                        float *mine = nbl + (sl & (ntab - 1)) * tab;
+                        if (NBLDS && ntab == TILE) {
+                            // a lane meets only its own adds: all steps' entries at once, a step that
+                            // repeats the symbol of an earlier one goes on from that one's sum
+                            float4 x[CS][R];
+                            auto at = [&](int u, int r) {
+                                return (float4 *)&mine[oc[u] * NP + ((16 * r + 4 * g) ^ (oc[u] * 4 & swz))];
+                            };
+#pragma unroll
+                            for (int u = 0; u < CS; ++u)
+#pragma unroll
+                                for (int r = 0; r < R; ++r) x[u][r] = *at(u, r);
+#pragma unroll
+                            for (int u = 0; u < CS; ++u) {
+#pragma unroll
+                                for (int r = 0; r < R; ++r) {
+#pragma unroll
+                                    for (int q = 0; q < u; ++q) {
+                                        const bool same = oc[q] == oc[u];
+                                        x[u][r].x = same ? x[q][r].x : x[u][r].x;
+                                        x[u][r].y = same ? x[q][r].y : x[u][r].y;
+                                        x[u][r].z = same ? x[q][r].z : x[u][r].z;
+                                        x[u][r].w = same ? x[q][r].w : x[u][r].w;
+                                    }
+                                    x[u][r].x += gm[u][r][0];
+                                    x[u][r].y += gm[u][r][1];
+                                    x[u][r].z += gm[u][r][2];
+                                    x[u][r].w += gm[u][r][3];
+                                    *at(u, r) = x[u][r];
+                                }
+                            }
+                        } else if (NBLDS) {
+                            int rank[CS];
+                            if (ntab == 1) {
+#pragma unroll
+                                for (int u = 0; u < CS; ++u) rank[u] = slot_rank(ranktab, oc[u], sl);
+                            } else {
+#pragma unroll
+                                for (int u = 0; u < CS; ++u) rank[u] = shared_rank(oc[u], ntab);
+                            }
+#pragma unroll
+                            for (int u = 0; u < CS; ++u) {
+                                partial_add<R>(mine, oc[u], swz, g, rank[u], gm[u]);
+                                wave_lds_sync();
+                            }
+                        } else {
+#pragma unroll
+                            for (int u = 0; u < CS; ++u)
+#pragma unroll
+                                for (int r = 0; r < R; ++r)
+#pragma unroll
+                                    for (int v = 0; v < 4; ++v) {
+                                        const float x = gm[u][r][v];
+                                        if (x != 0.0f && __builtin_isfinite(x))
+                                            atomicAdd(&B64k[(size_t)oc[u] * NP + quad_t(16 * r + 4 * g + v)], to_fixed(x, F));
+                                    }
+                        }
+                        if (c.t0 < CS) {  // the sequences' first steps
+#pragma unroll
+                            for (int r = 0; r < R; ++r)
+#pragma unroll
+                                for (int v = 0; v < 4; ++v) {
+                                    const int i = 16 * r + 4 * g + v;
+                                    float x = 0.0f;
+#pragma unroll
+                                    for (int u = 0; u < CS; ++u) x = c.t0 == u ? gm[u][r][v] : x;
+                                    if (i < N) add_fixed(&a.pi64[(size_t)k * N + i], x, F, &a.nanflag[k]);
+                                }
+                        }
+                    };
+                    Chunk cp{0, 0};
+                    int half_ring = 0;
+                    for (int p = 0; p <= nseg; ++p) {
+                        const int j = nseg - p;
+                        const float4 *sa = seg_alpha(j);
+                        lds_barrier();
+                        for (int s = 0; s < nch; ++s, half_ring ^= 1) {
+                            const Chunk cn = back_chunk(j, s);
+#pragma unroll
+                            for (int u = 0; u < CS; ++u) {
+#pragma unroll
+                                for (int r = 0; r < R; ++r)
+                                    an[u][r] = sa[(size_t)(max(cn.n - 1 - u, 0) * R + r) * WAVE + lane];
+                                on[u] = load_sym(cn.t0 - u);
+                            }
+                            if (cp.n > 0) take(cp, half_ring ^ 1);
+                            // (as in XI)
+#pragma unroll
+                            for (int u = 0; u < CS; ++u) {
+                                oc[u] = checked(on[u]);
+#pragma unroll
+                                for (int r = 0; r < R; ++r) ac[u][r] = an[u][r];
+                            }
+                            cp = cn;
+                            lds_barrier();
+                        }
                     }
-                    wave_lds_sync();
+                    if (cp.n > 0) take(cp, half_ring ^ 1);
+                    if (!__builtin_isfinite(nan_acc)) atomicOr(&a.nanflag[k], 1);
+                }
+            }  // Tmax > 0
+            if (NBLDS) {
+                // the tile's emission partial into its slab slot (zeros for an empty tile)
+                __syncthreads();
+                const int64_t slot = slab_slot(gbeg, k, tile);
+                float *dst = a.slab + (size_t)(dbg_in(slot, slab_slots(a.S, a.K), HMM_DEBUG_SLAB) ? slot : 0) * M * NP;
+                for (int idx = threadIdx.x; idx < M * NP; idx += ROLES * WAVE) {
+                    const int o = idx / NP, ic = idx % NP;
+                    float v = 0.0f;
+                    for (int n = 0; n < ntab; ++n) {
+                        v += nbl[n * tab + idx];
+                        nbl[n * tab + idx] = 0.0f;
+                    }
+                    dst[(size_t)o * NP + (ic ^ (o * 4 & swz))] = v;
                 }
             }
         }
     }
 }
 
-template <int R, int WAVES, bool NBLDS>
-size_t adj_lds_bytes(int M) {
-    return (NBLDS ? (size_t)M * 16 * R * 4 + (size_t)M * 4 : 0) + (size_t)WAVES * AdjShape<R>::per_wave_bytes;
+constexpr size_t LDS_CU = 160 * 1024;
+constexpr size_t LDS_GRANULE = 1280;  // workgroups take LDS in units of this
+
+// LDS for the emission partial of one workgroup in `tables` tables.
+size_t partial_bytes(int NP, int M, int tables) {
+    return (size_t)tables * (M + 1) * NP * 4 + (tables == 1 ? (size_t)((M + 1) / 2) * 4 : 0);
 }
 
-template <int R, int WAVES, bool NBLDS>
-int occupancy_grid(int M, int cu_count, int K, bool set_attr) {
-    auto kern = k_adj_mfma<R, WAVES, NBLDS>;
-    const size_t lds = adj_lds_bytes<R, WAVES, NBLDS>(M);
-    if (set_attr && lds > 64 * 1024)
-        (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds);
-    int per_cu = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, WAVES * WAVE, lds) != hipSuccess || per_cu < 1)
-        per_cu = 1;
-    int grid = cu_count * per_cu;
-    if (K > 0 && grid >= K) grid = (grid / K) * K;
-    return grid;
-}
-
-constexpr size_t LDS_LIMIT = 160 * 1024;
-
-// Which variant a shape takes: a one-wave workgroup with the emission partial in
-// LDS (when it fits and the slab of per-tile partials stays within
-// SLAB_MAX_BYTES), else four waves adding to the global counts.
+// Which variant a shape takes: the emission partial in LDS (when it fits and the slab of
+// per-tile partials stays within SLAB_MAX_BYTES), else adds to the global counts.
 template <int R>
 bool use_partial(int M, int S, int K) {
     if (slab_slots(S, K) * M * 16 * R * 4 > SLAB_MAX_BYTES) return false;
-    return adj_lds_bytes<R, 1, true>(M) <= LDS_LIMIT;
+    return partial_bytes(16 * R, M, 1) + AdjShape<R, 2>::static_bytes <= LDS_CU;
 }
 
+// Workgroups per CU that the tiles can fill, within what the registers allow.
 template <int R>
-int grid_for(int M, int S, int cu_count, int K, bool set_attr, int *waves) {
+int want_per_cu(int S, int K, int cu_count) {
+    const int64_t n = (tile_bound(S, K, false, TILE) + cu_count - 1) / cu_count;
+    return (int)std::min<int64_t>(std::max<int64_t>(n, 1), adj_waves(R, 2));
+}
+
+// Tables of the LDS partial in a workgroup whose LDS is its share of a CU's.  Slots that share
+// a symbol and a table add one after the other, an LDS round trip each, and one table needs
+// slot_rank besides, so as many as fit; never at the cost of a resident workgroup.
+template <int R, int CS>
+int tables_for(int M, int want) {
+    const size_t share = LDS_CU / want / LDS_GRANULE * LDS_GRANULE;
+    for (int n = TILE; n > 1; n /= 2)
+        if (partial_bytes(16 * R, M, n) + AdjShape<R, CS>::static_bytes <= share) return n;
+    return 1;
+}
+
+// The kernel, LDS and tables of a launch, and the grid that the card holds at once.
+struct AdjPlan {
+    void (*kern)(DevPtrs, AdjLaunch);
+    size_t lds;
+    int ntab, grid;
+};
+
+template <int R>
+AdjPlan plan_for(int M, int S, int cu_count, int K) {
+    AdjPlan p{k_adj_tile<R, false, 2>, 0, 1, 0};
     if (use_partial<R>(M, S, K)) {
-        *waves = 1;
-        return occupancy_grid<R, 1, true>(M, cu_count, K, set_attr);
+        const int want = want_per_cu<R>(S, K, cu_count);
+        // Four steps per chunk halve the barriers of a tile that has its CU to itself; with more
+        // of them on a CU, two steps take fewer registers and less LDS.  One iteration of
+        // training at 8 states took 777 us with four and 807 with two (300 sequences of 20-1500
+        // on 30 symbols), and 762 and 729 us (40000 sequences of 50-600 on 6).
+        constexpr int WIDE = R == 1 ? 4 : 2;
+        if (want == 1 && partial_bytes(16 * R, M, 1) + AdjShape<R, WIDE>::static_bytes <= LDS_CU) {
+            p.kern = k_adj_tile<R, true, WIDE>;
+            p.ntab = tables_for<R, WIDE>(M, want);
+        } else {
+            p.kern = k_adj_tile<R, true, 2>;
+            p.ntab = tables_for<R, 2>(M, want);
+        }
+        p.lds = partial_bytes(16 * R, M, p.ntab);
+        if (p.lds > 64 * 1024)
+            (void)hipFuncSetAttribute((const void *)p.kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds);
     }
-    *waves = 4;
-    return occupancy_grid<R, 4, false>(M, cu_count, K, set_attr);
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, p.kern, ROLES * WAVE, p.lds) != hipSuccess || per_cu < 1)
+        per_cu = 1;
+    p.grid = cu_count * per_cu;
+    if (K > 0 && p.grid >= K) p.grid = (p.grid / K) * K;
+    return p;
 }
 
 template <int R>
-hipError_t launch_r(const DevPtrs &d, const AdjLaunch &a, int cu_count, hipStream_t st) {
-    int waves = 4;
-    const int full = grid_for<R>(a.M, a.S, cu_count, a.K, true, &waves);
-    const int grid = persistent_grid(full, tile_bound(a.S, a.K, false, TILE), waves, a.K, a.max_grid);
-    if (grid * waves > a.seg_slots) return hipErrorInvalidValue;
-    if (use_partial<R>(a.M, a.S, a.K)) {
-        if (a.slab == nullptr) return hipErrorInvalidValue;
-        k_adj_mfma<R, 1, true><<<grid, WAVE, adj_lds_bytes<R, 1, true>(a.M), st>>>(d, a);
-    } else {
-        if (a.B64 == nullptr) return hipErrorInvalidValue;
-        k_adj_mfma<R, 4, false><<<grid, 4 * WAVE, adj_lds_bytes<R, 4, false>(a.M), st>>>(d, a);
-    }
+hipError_t launch_r(const DevPtrs &d, AdjLaunch a, int cu_count, hipStream_t st) {
+    const AdjPlan p = plan_for<R>(a.M, a.S, cu_count, a.K);
+    const int grid = persistent_grid(p.grid, tile_bound(a.S, a.K, false, TILE), 1, a.K, a.max_grid);
+    if (grid > a.seg_slots) return hipErrorInvalidValue;
+    if (use_partial<R>(a.M, a.S, a.K) ? a.slab == nullptr : a.B64 == nullptr) return hipErrorInvalidValue;
+    a.ntab = p.ntab;
+    p.kern<<<grid, ROLES * WAVE, p.lds, st>>>(d, a);
     return hipGetLastError();
 }
 
 }  // namespace
 
-bool adj_mfma_supported(int NP) { return NP == 16 || NP == 32 || NP == 48 || NP == 64; }
+bool adj_mfma_supported(int NP) { return NP == 16 || NP == 32 || NP == 48; }
 
 bool adj_mfma_slab(int NP, int M, int S, int K) {
     switch (NP / 16) {
         case 1: return use_partial<1>(M, S, K);
         case 2: return use_partial<2>(M, S, K);
         case 3: return use_partial<3>(M, S, K);
-        case 4: return use_partial<4>(M, S, K);
         default: return false;
     }
 }
 
 int adj_mfma_slots(int NP, int M, int S, int K, int cu_count) {
-    int waves = 4, grid = 0;
     switch (NP / 16) {
-        case 1: grid = grid_for<1>(M, S, cu_count, K, true, &waves); break;
-        case 2: grid = grid_for<2>(M, S, cu_count, K, true, &waves); break;
-        case 3: grid = grid_for<3>(M, S, cu_count, K, true, &waves); break;
-        case 4: grid = grid_for<4>(M, S, cu_count, K, true, &waves); break;
+        case 1: return plan_for<1>(M, S, cu_count, K).grid;
+        case 2: return plan_for<2>(M, S, cu_count, K).grid;
+        case 3: return plan_for<3>(M, S, cu_count, K).grid;
         default: return 0;
     }
-    return grid * waves;
 }
 
 int64_t adj_mfma_seg_stride(int NP, int max_len) {
     int L = 1;
     while ((int64_t)L * L < max_len) ++L;
-    return (int64_t)L * WAVE * (4 * (NP / 16) + 2);
+    return (int64_t)2 * L * WAVE * (4 * (NP / 16) + 1);
 }
 
 hipError_t launch_adj_mfma(const DevPtrs &d, const AdjLaunch &a, int cu_count, hipStream_t st) {
@@ -472,7 +732,6 @@ hipError_t launch_adj_mfma(const DevPtrs &d, const AdjLaunch &a, int cu_count, h
         case 1: return launch_r<1>(d, a, cu_count, st);
         case 2: return launch_r<2>(d, a, cu_count, st);
         case 3: return launch_r<3>(d, a, cu_count, st);
-        case 4: return launch_r<4>(d, a, cu_count, st);
         default: return hipErrorInvalidValue;
     }
 }

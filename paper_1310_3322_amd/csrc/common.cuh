@@ -132,17 +132,18 @@ __device__ __forceinline__ void add_fixed(unsigned long long *dst, float v, int 
 }
 
 // Slot order of repeated symbols in one step of a 16-sequence tile: each of the
-// wave's lanes of slot `sl` sets bit sl in the entry of its symbol in `tab`
-// (an LDS atomic OR, order-independent), reads the entry back and clears it;
-// returns how many lower slots share the symbol (0 for the first occurrence).
-// Adds to an LDS partial then go in rounds of equal rank, so the result does
-// not depend on how the LDS serialises lanes that collide.
+// wave's lanes of slot `sl` sets bit sl of its symbol's mask in `tab` (two 16-bit
+// masks per word, symbols o and o ^ 1; an LDS atomic OR, order-independent), reads
+// the mask back and clears the word; returns how many lower slots share the symbol
+// (0 for the first occurrence).  Adds to an LDS partial then go in rounds of equal
+// rank, so the result does not depend on how the LDS serialises lanes that collide.
 __device__ __forceinline__ int slot_rank(uint32_t *tab, int sym, int sl) {
-    atomicOr(&tab[sym], 1u << sl);
+    const int sh = (sym & 1) << 4;
+    atomicOr(&tab[sym >> 1], 1u << (sh + sl));
     wave_lds_sync();
-    const uint32_t m = tab[sym];
+    const uint32_t m = (tab[sym >> 1] >> sh) & 0xffffu;
     wave_lds_sync();
-    tab[sym] = 0u;
+    tab[sym >> 1] = 0u;
     return __popc(m & ((1u << sl) - 1u));
 }
 

@@ -57,7 +57,7 @@ struct Layout {
     int32_t plan_chunk;    // sequences per chunk of the stable counting sort
     int32_t plan_nchunks;  // chunks of the stable counting sort
     int32_t nck;         // checkpoints per sequence slot
-    int32_t seg_slots;   // persistent waves of the gradient kernel
+    int32_t seg_slots;   // persistent workgroups of the gradient kernel
     int64_t seg_stride;  // floats per segment slot
 };
 
@@ -271,6 +271,7 @@ struct AdjLaunch {
     const float *mlast;
     const int64_t *rowpos;
     int64_t grad_rows;
+    int ntab;  // tables of the LDS emission partial (set by the launcher)
 };
 // Whether a gradient call stores every step's alphahat (decided on the device
 // from the row prefix, so that overlapping sequences whose rows exceed the
