@@ -625,7 +625,7 @@ __global__ void __launch_bounds__(R / BO * WAVE) k_adj_coop(DevPtrs d, AdjLaunch
                     for (int b = 0; b < BO; ++b)
 #pragma unroll
                         for (int v = 0; v < 4; ++v)
-                            if (ib + 16 * b + v < N) add_fixed(&a.pi64[rb + 16 * b + v], gpi[b][v], F, &a.nanflag[k]);
+                            if (ib + 16 * b + v < N) add_fixed_slots(&a.pi64[rb + 16 * b + v], gpi[b][v], F, &a.nanflag[k], sl);
 #pragma unroll
                     for (int b = 0; b < BO; ++b)
 #pragma unroll
@@ -1006,7 +1006,7 @@ __global__ void __launch_bounds__(2 * R * WAVE) k_adj_pipe(DevPtrs d, AdjLaunch 
 #pragma unroll
                     for (int v = 0; v < 4; ++v) {
                         const int i = 16 * w + 4 * g + v;
-                        if (i < N) add_fixed(&a.pi64[(size_t)k * N + i], gpi[v], F, &a.nanflag[k]);
+                        if (i < N) add_fixed_slots(&a.pi64[(size_t)k * N + i], gpi[v], F, &a.nanflag[k], sl);
                     }
                     if (lane_nan) atomicOr(&a.nanflag[k], 1);
                 }

@@ -564,7 +564,7 @@ k_adj_tile(DevPtrs d, AdjLaunch a) {
                                     float x = 0.0f;
 #pragma unroll
                                     for (int u = 0; u < CS; ++u) x = c.t0 == u ? gm[u][r][v] : x;
-                                    if (i < N) add_fixed(&a.pi64[(size_t)k * N + i], x, F, &a.nanflag[k]);
+                                    if (i < N) add_fixed_slots(&a.pi64[(size_t)k * N + i], x, F, &a.nanflag[k], sl);
                                 }
                         }
                     };
