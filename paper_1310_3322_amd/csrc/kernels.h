@@ -79,6 +79,28 @@ inline int persistent_grid(int occ_grid, int64_t items_bound, int items_per_wg, 
     return grid > 0 ? grid : 1;
 }
 
+// Rank of workgroup i of a model's n in the model's list of tiles, longest first, when each
+// takes its first tiles by rank.  Workgroups are placed on the CUs in turns of the CU
+// count, so i, i + turn, .. (turn = CUs / K) share a CU; ranks run backwards and forwards
+// in alternate turns, which gives each CU long and short tiles alike, and leaves the
+// longest without company where the last turn is short.
+__device__ __forceinline__ int first_rank(int i, int n, int turn) {
+    if (n <= turn) return i;
+    const int t = i / turn, b = t * turn;
+    const int len = n - b < turn ? n - b : turn;
+    return t & 1 ? i : b + len - 1 - (i - b);
+}
+
+// Priority of a wave whose tile is of the given turn.
+__device__ __forceinline__ void set_tile_priority(int turn) {
+    switch (turn) {
+        case 0: __builtin_amdgcn_s_setprio(3); break;
+        case 1: __builtin_amdgcn_s_setprio(2); break;
+        case 2: __builtin_amdgcn_s_setprio(1); break;
+        default: __builtin_amdgcn_s_setprio(0); break;
+    }
+}
+
 // XCDs of MI355X; workgroup b of a launch runs on XCD b mod XCDS.
 constexpr int XCDS = 8;
 // Tile slices of an all-pairs forward: one per XCD when every (model, XCD) pair
@@ -196,6 +218,7 @@ struct FwdLaunch {
     int64_t grad_rows;
     int max_grid;     // cap on the persistent grid (0: occupancy limit)
     int tune_flags;   // HMM_TUNE_* of the call
+    int nwg, turn;    // workgroups per model and first_rank's turn (set by the launcher)
 };
 // Whether a tile forward copies the emission table (M x NP floats) into LDS.
 inline bool bt_in_lds(const FwdLaunch &f) {
