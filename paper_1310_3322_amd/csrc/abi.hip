@@ -671,15 +671,6 @@ hmm_status hmm_forward_backward_grad(const hmm_bank *bank, const hmm_batch *batc
     if (phase == 1) return HMM_OK;
     const bool coop = grad_uses_coop(NP);
     const bool slab = L.slab_on != 0;
-    // the fixed-point count sums start at zero (fill kernels: no memset nodes in a captured graph)
-    launch_fill_i32((int32_t *)(w + L.pi64), (size_t)2 * K * N, 0, stream);
-    launch_fill_i32((int32_t *)(w + L.A64), (size_t)2 * K * N * N, 0, stream);
-    if (!slab) launch_fill_i32((int32_t *)(w + L.B64), (size_t)2 * K * M * NP, 0, stream);
-    launch_fill_i32((int32_t *)(w + L.nanflag), (size_t)K, 0, stream);
-    launch_weight_max(seq_weight, S, (uint32_t *)(w + L.wmax), stream);
-    int32_t *queue2 = (int32_t *)(w + L.queue) + queue_heads(K);
-    launch_fill_i32(queue2, (size_t)K, 0, stream);
-    if (hipGetLastError() != hipSuccess) return HMM_ERR_HIP;
     AdjLaunch a;
     memset(&a, 0, sizeof(a));
     a.K = K;
@@ -691,7 +682,7 @@ hmm_status hmm_forward_backward_grad(const hmm_bank *bank, const hmm_batch *batc
     a.total = batch->total_symbols;
     a.perm = (const int32_t *)(w + L.perm);
     a.gstart = (const int32_t *)(w + L.gstart);
-    a.queue = queue2;
+    a.queue = (int32_t *)(w + L.queue) + queue_heads(K);
     a.err = err;
     a.bt = (const float *)(w + L.bt);
     a.ckpt = (const float *)(w + L.ckpt);
@@ -723,6 +714,9 @@ hmm_status hmm_forward_backward_grad(const hmm_bank *bank, const hmm_batch *batc
         a.rowpos = (const int64_t *)(w + L.rowpos);
         a.grad_rows = L.grad_rows;
     }
+    // the fixed-point count sums start at zero (no memset nodes in a captured graph)
+    launch_grad_init(a, (uint32_t *)(w + L.wmax), stream);
+    if (hipGetLastError() != hipSuccess) return HMM_ERR_HIP;
     if (S > 0) {
         if (coop && adj_coop_streams(NP)) {
             float *frag = (float *)(w + L.frag);

@@ -322,7 +322,7 @@ constexpr int64_t SLAB_MAX_BYTES = (int64_t)1 << 30;
 // Final counts: n_pi and n_A from the fixed-point sums, n_B from the slab (tiles of
 // each model summed in tile order) or the fixed-point sums, NaN for flagged models.
 void launch_counts_finish(const AdjLaunch &a, bool slab, float *cnt_pi, float *cnt_A, float *cnt_B, hipStream_t st);
-void launch_weight_max(const float *w, int S, uint32_t *wmax, hipStream_t st);
+void launch_grad_init(const AdjLaunch &a, uint32_t *wmax, hipStream_t st);
 // adj_coop.hip: cooperative-tile backward (one wave per 16-state block)
 bool adj_coop_supported(int NP);
 bool adj_coop_streams(int NP);  // fragments streamed from the workspace (launch_coop_frags first)

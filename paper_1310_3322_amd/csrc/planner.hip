@@ -8,6 +8,7 @@
 // sequence is scored against every model.  Tiles of 16 consecutive entries of
 // that order then hold sequences of nearly equal length, and the longest tiles
 // are handed out first.
+#include <algorithm>
 #include <climits>
 #include <cstring>
 
@@ -492,12 +493,12 @@ __global__ void __launch_bounds__(1024) k_plan_one(DevPtrs d, int S, int K, int 
 // count.  Tiles of 32 states x 8 symbols through LDS, so both sides are read
 // and written in rows; one element per thread, the slab's partials requested 8
 // at a time (the sum still takes them in tile order).
-__global__ void k_counts_finish_b(AdjLaunch a, int slab, float *cnt_B) {
+__device__ __forceinline__ void finish_b(const AdjLaunch &a, int slab, float *cnt_B, int blk) {
     __shared__ float tile[8][33];
-    const int k = blockIdx.z;
     const int N = a.N, M = a.M, NP = a.NP;
-    const int i0 = blockIdx.x * 32, o0 = blockIdx.y * 8;
-    const int tx = threadIdx.x, ty = threadIdx.y;
+    const int bx = (N + 31) / 32, by = (M + 7) / 8;
+    const int k = blk / (bx * by), i0 = blk % bx * 32, o0 = blk / bx % by * 8;
+    const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
     {
         const int o = o0 + ty, i = i0 + tx;
         float v = 0.0f;
@@ -525,12 +526,18 @@ __global__ void k_counts_finish_b(AdjLaunch a, int slab, float *cnt_B) {
     if (i < N && o < M) dst[(size_t)i * M + o] = bad ? __builtin_nanf("") : tile[f % 8][f / 8];
 }
 
-// cnt_pi [K][N] and cnt_A [K][N][N] from their fixed-point sums.
-__global__ void k_counts_finish_pa(AdjLaunch a, float *cnt_pi, float *cnt_A) {
+// cnt_pi [K][N] and cnt_A [K][N][N] from their fixed-point sums (the first pa_blocks), and cnt_B
+// (the others), in one launch.
+__global__ void __launch_bounds__(256) k_counts_finish(AdjLaunch a, int pa_blocks, int slab, float *cnt_pi, float *cnt_A,
+                                                       float *cnt_B) {
+    if ((int)blockIdx.x >= pa_blocks) {
+        finish_b(a, slab, cnt_B, (int)blockIdx.x - pa_blocks);
+        return;
+    }
     const int N = a.N, K = a.K;
     const int F = fixed_exponent(*a.wmax, a.S, a.max_len);
     const int64_t npi = (int64_t)K * N, nA = (int64_t)K * N * N;
-    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    const int64_t stride = (int64_t)pa_blocks * blockDim.x;
     for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < npi + nA; i += stride) {
         if (i < npi) {
             const int k = (int)(i / N);
@@ -541,6 +548,22 @@ __global__ void k_counts_finish_pa(AdjLaunch a, float *cnt_pi, float *cnt_A) {
             cnt_A[j] = a.nanflag[k] ? __builtin_nanf("") : from_fixed(a.A64[j], F);
         }
     }
+}
+
+// The sums, flags, queue heads and scale of a gradient's backward pass at their starts, in one
+// launch (six fills took 20 us of a small call).
+__global__ void __launch_bounds__(256) k_grad_init(AdjLaunch a, uint32_t *wmax, uint32_t wbits) {
+    const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+    const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+    const int64_t npi = (int64_t)a.K * a.N, nA = npi * a.N, nB = a.B64 ? (int64_t)a.K * a.M * a.NP : 0;
+    for (int64_t i = i0; i < npi; i += stride) a.pi64[i] = 0;
+    for (int64_t i = i0; i < nA; i += stride) a.A64[i] = 0;
+    for (int64_t i = i0; i < nB; i += stride) a.B64[i] = 0;
+    for (int64_t i = i0; i < a.K; i += stride) {
+        a.nanflag[i] = 0;
+        a.queue[i] = 0;
+    }
+    if (i0 == 0) *wmax = wbits;
 }
 
 // *wmax = bits of max_s |w_s| over the finite weights (non-negative floats order
@@ -855,21 +878,21 @@ void launch_counts_finish(const AdjLaunch &a, bool slab, float *cnt_pi, float *c
     const int64_t n = (int64_t)a.K * a.N * (1 + a.N);
     int nb = blocks_for(n, 256);
     if (nb > 8192) nb = 8192;
-    hipLaunchKernelGGL(k_counts_finish_pa, dim3(nb), dim3(256), 0, st, a, cnt_pi, cnt_A);
-    dim3 grid((a.N + 31) / 32, (a.M + 7) / 8, a.K);
-    hipLaunchKernelGGL(k_counts_finish_b, grid, dim3(32, 8), 0, st, a, slab ? 1 : 0, cnt_B);
+    const int64_t b_blocks = (int64_t)((a.N + 31) / 32) * ((a.M + 7) / 8) * a.K;
+    hipLaunchKernelGGL(k_counts_finish, dim3((unsigned)(nb + b_blocks)), dim3(256), 0, st, a, nb, slab ? 1 : 0, cnt_pi, cnt_A,
+                       cnt_B);
 }
 
-void launch_weight_max(const float *w, int S, uint32_t *wmax, hipStream_t st) {
-    if (w == nullptr) {
-        launch_fill_i32((int32_t *)wmax, 1, (int32_t)0x3f800000, st);  // 1.0f: unit weights
-        return;
-    }
-    launch_fill_i32((int32_t *)wmax, 1, 0, st);
-    if (S > 0) {
-        int nb = blocks_for(S, 256);
+void launch_grad_init(const AdjLaunch &a, uint32_t *wmax, hipStream_t st) {
+    const int64_t n = (int64_t)a.K * (a.B64 ? std::max(a.N * a.N, a.M * a.NP) : a.N * a.N);
+    int nb = blocks_for(n, 256);
+    if (nb > 8192) nb = 8192;
+    // the scale of unit weights is 1.0f, that of others the maximum of the next launch
+    hipLaunchKernelGGL(k_grad_init, dim3(nb), dim3(256), 0, st, a, wmax, a.weight ? 0u : 0x3f800000u);
+    if (a.weight && a.S > 0) {
+        nb = blocks_for(a.S, 256);
         if (nb > 1024) nb = 1024;
-        hipLaunchKernelGGL(k_weight_max, dim3(nb), dim3(256), 0, st, w, S, wmax);
+        hipLaunchKernelGGL(k_weight_max, dim3(nb), dim3(256), 0, st, a.weight, a.S, wmax);
     }
 }
 
