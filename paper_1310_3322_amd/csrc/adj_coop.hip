@@ -1039,6 +1039,268 @@ __global__ void __launch_bounds__(2 * R * WAVE) k_adj_pipe(DevPtrs d, AdjLaunch 
     }
 }
 
+// Walk over the stored rows with the LDS partial: 2 R waves per tile, one barrier per
+// step.  Wave w < R (the chain) forms its block of betahat_t and w_t; wave R + w takes the
+// same block one step later: C += X^T W for its rows, and the emission counts.  The chain
+// leaves w_{t+1} in a ring of three exchange rows and betahat_t in one of two.  Symbols and
+// exponents travel in chunks of DSEG steps, held in registers for a chunk before they enter
+// LDS; stored rows are requested two steps ahead, emission rows one.  Every quantity is
+// formed by the same operations in the same order as in k_adj_coop.
+//
+// Bound by the vector and matrix instructions of a SIMD: at 64 states 1024 cycles of FP32
+// matrix instructions per step, which leave no slot to vector instructions; in k_adj_coop a SIMD
+// had one wave and waited besides for its LDS reads and its adds to the partial.  A gradient
+// step of 8 models of 64 states with 512 symbols, 8192 sequences of 100-1000, went from 2460 to
+// 2285 us; counts of 3000 sequences of 100-900 under 6 models of 96 states with 200 symbols from 2.97
+// to 2.52 ms.  The emission counts as a third part (12 waves at 64 states) took 2330 us.
+constexpr int DSEG = 16;
+
+template <int R>
+struct AdjDuoShape {
+    static constexpr int XROW = CoopShape<R>::XROW;
+    static constexpr int static_bytes =
+        (3 * TILE * XROW + R * TILE * 17 + 4 * DSEG * TILE) * 4 + 2 * R * WAVE * 16 + 64;
+};
+
+template <int R>
+__global__ void __launch_bounds__(2 * R * WAVE) k_adj_duo(DevPtrs d, AdjLaunch a) {
+    if (!grad_full(a.arow, a.rowpos, a.S, a.grad_rows)) return;
+    constexpr int NP = 16 * R, XROW = CoopShape<R>::XROW;
+    extern __shared__ __align__(16) unsigned char smem[];
+    __shared__ __align__(16) float wring[3][TILE * XROW];      // w_t at t mod 3
+    __shared__ __align__(16) float4 bring[2][R][WAVE];         // betahat_t at t mod 2
+    __shared__ float atile_all[R * TILE * 17];
+    __shared__ int32_t seg[2][2][DSEG * TILE];                 // [chunk parity][symbol, exponent]
+    __shared__ int32_t tile_sh;
+    float *nbl = (float *)smem;  // [M][NP] emission-count partial
+    // [2][ceil(M / 2)] words after the partial: slot masks of the symbols of a step
+    uint32_t *ranktab = (uint32_t *)(smem + (size_t)a.M * NP * 4);
+    const int m2 = (a.M + 1) / 2;
+
+    const int lane = threadIdx.x & (WAVE - 1);
+    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x / WAVE);
+    const bool chain = wid < R;
+    const int w = chain ? wid : wid - R;  // owned 16-state block
+    const int sl = lane & 15, g = lane >> 4;
+    const int K = a.K, N = a.N, M = a.M;
+    const int swz = nb_swz(NP);
+    const int F = fixed_exponent(*a.wmax, a.S, a.max_len);
+    float *atile = atile_all + w * TILE * 17;  // [16 s][17] own alphahat block, transposed reads
+
+    int k_first, k_step;
+    model_walk(K, (int)gridDim.x, (int)blockIdx.x, &k_first, &k_step);
+    for (int k = k_first; k < K; k += k_step) {
+        const int gbeg = a.gstart[k], gend = a.gstart[k + 1];
+        const int ntiles = (gend - gbeg + TILE - 1) / TILE;
+        const float *btk = a.bt + (size_t)k * M * NP;
+        if (ntiles == 0) continue;
+        __syncthreads();
+        for (int i = threadIdx.x; i < M * NP; i += blockDim.x) nbl[i] = 0.0f;
+        for (int i = threadIdx.x; i < 2 * m2; i += blockDim.x) ranktab[i] = 0u;
+        const float *Ak = d.A + (size_t)k * N * N;
+        float ab[1][R][4];
+        if (chain) coop_load_bwd_fragments<R, 1>(ab, Ak, N, w, g, sl);
+
+        for (;;) {
+            __syncthreads();
+            if (threadIdx.x == 0) tile_sh = atomicAdd(&a.queue[k], 1);
+            __syncthreads();
+            const int tile = __builtin_amdgcn_readfirstlane(tile_sh);  // scalar exit: the loop holds barriers
+            if (tile >= ntiles) break;
+
+            const int pos = gbeg + tile * TILE + sl;
+            const bool has = pos < gend;
+            const int seq = has ? a.perm[pos] : 0;
+            int32_t T = 0;
+            int64_t off = 0;
+            bool act = false;
+            if (has) {
+                T = d.lengths[seq];
+                off = d.offsets[seq];
+                const int mk = d.model_of_seq[seq];
+                const bool bad = seq_bad(T, off, a.max_len, a.total) || mk < 0 || mk >= K;
+                if (bad) T = 0;
+                act = !bad && T > 0 && a.flag[pos] == 0;
+            }
+            const int Tmax = __builtin_amdgcn_readfirstlane(wave_max_int(T));
+            if (Tmax > 0) {
+                const float wgt = act ? (a.weight ? a.weight[seq] : 1.0f) : 0.0f;
+                const int32_t *sbase = T > 0 ? d.symbols + off : d.symbols;
+                const int64_t rb = T > 0 ? a.rowpos[pos] : 0;  // first stored row of the sequence
+                // stored row of step t (steps past the sequence's end: its last row, not used)
+                auto row_of = [&](int t) {
+                    int64_t row = T > 0 ? rb + min(max(t, 0), T - 1) : 0;
+                    if (!dbg_in(row, a.grad_rows, HMM_DEBUG_GRAD_ROWS)) row = 0;
+                    return row;
+                };
+                // The thread's entry of the chunk of steps t, t - 1, .. (of its own slot):
+                // symbols by the first DSEG * TILE threads, exponents by the next.
+                const int cs = (int)threadIdx.x / TILE % DSEG, half = (int)threadIdx.x / (TILE * DSEG);
+                auto load_entry = [&](int t) {
+                    const int ts = max(t - cs, 0);
+                    if (half == 0) {
+                        const int o = sbase[min(ts, T > 0 ? T - 1 : 0)];
+                        return (unsigned)o < (unsigned)M ? o : 0;
+                    }
+                    return half == 1 ? a.aexp[row_of(ts)] : 0;
+                };
+                auto store_entry = [&](int c, int v) {
+                    if (half < 2) seg[c & 1][half][cs * TILE + sl] = v;
+                };
+                auto entry = [&](int t, int what) {  // symbol (0) or exponent (1) of step t
+                    const int i = Tmax - 1 - t;
+                    return seg[i / DSEG & 1][what][i % DSEG * TILE + sl];
+                };
+                store_entry(0, load_entry(Tmax - 1));
+                int nxt = load_entry(Tmax - 1 - DSEG);
+                for (int i = threadIdx.x; i < TILE * XROW; i += blockDim.x) wring[Tmax % 3][i] = 0.0f;  // w of step Tmax
+                __syncthreads();
+                // the next chunk's entries, a step before its first is read
+                auto advance = [&](int t) {
+                    const int i = Tmax - 1 - t;
+                    if (i % DSEG == DSEG - 2) {
+                        store_entry(i / DSEG + 1, nxt);
+                        nxt = load_entry(t - 1 - DSEG - 1);
+                    }
+                };
+                if (chain) {
+                    const float m_last = T > 0 ? a.mlast[pos] : 1.0f;
+                    float4 bb = *(const float4 *)&btk[(size_t)entry(Tmax - 1, 0) * NP + 16 * w + 4 * g];
+                    int slot = Tmax % 3;  // of w_{t+1}
+                    for (int t = Tmax - 1; t >= 0; --t) {
+                        const float4 b = bb;
+                        const int et = entry(t, 1);
+                        if (t > 0) bb = *(const float4 *)&btk[(size_t)entry(t - 1, 0) * NP + 16 * w + 4 * g];
+                        floatx4 be[1];
+                        coop_matvec<R, 1>(ab, wring[slot], 0, g, sl, be);
+                        if (t == T - 1) {
+                            const float inv = 1.0f / m_last;
+#pragma unroll
+                            for (int v = 0; v < 4; ++v) be[0][v] = inv;
+                        }
+                        bring[t & 1][w][lane] = float4{be[0][0], be[0][1], be[0][2], be[0][3]};
+                        // w_t = b_t o betahat_t 2^-e_t; zero where the sequence has ended or takes
+                        // no part (its values may be inf / NaN)
+                        const bool live = act && t < T;
+                        slot = slot == 0 ? 2 : slot - 1;
+                        *(float4 *)&wring[slot][sl * XROW + 16 * w + 4 * g] =
+                            float4{live ? ldexp_f(b.x * be[0][0], -et) : 0.0f, live ? ldexp_f(b.y * be[0][1], -et) : 0.0f,
+                                   live ? ldexp_f(b.z * be[0][2], -et) : 0.0f, live ? ldexp_f(b.w * be[0][3], -et) : 0.0f};
+                        advance(t);
+                        lds_barrier();
+                    }
+                    lds_barrier();
+                } else {
+                    floatx4 C[R];  // rows 16 w + 4 g + v, columns 16 rj + sl
+#pragma unroll
+                    for (int rj = 0; rj < R; ++rj) C[rj] = floatx4{0.0f, 0.0f, 0.0f, 0.0f};
+                    float gpi[4] = {};
+                    bool lane_nan = false;
+                    int rank_prev = 0;
+                    bool rank_has_prev = false;
+                    auto load_row = [&](int t) { return *(const float4 *)&a.arow[(size_t)row_of(t) * NP + 16 * w + 4 * g]; };
+                    int o_next = 0;  // symbol of the step of the next phase
+                    // the phase in which the chain forms step t: step t + 1, whose row is in al
+                    // (which then receives the row of step t - 1)
+                    auto phase = [&](int t, float4 &al) {
+                        const int s = t + 1, ot = o_next;
+                        if (t >= 0) {
+                            o_next = entry(t, 0);
+                            advance(t);
+                        }
+                        const bool live = act && s < T, trans = act && s + 1 < T;
+                        const float *wrow = wring[(s + 1) % 3];
+                        const float x[4] = {wgt * al.x, wgt * al.y, wgt * al.z, wgt * al.w};
+                        al = load_row(t - 1);
+                        const float4 be = bring[s & 1][w][lane];
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) atile[sl * 17 + 4 * g + v] = trans ? x[v] : 0.0f;
+                        const int rank = slot_rank_shared(ranktab, m2, ot, s & 1, rank_prev, rank_has_prev, sl);
+                        rank_prev = ot;
+                        rank_has_prev = true;
+                        wave_lds_sync();
+                        float xa[4], wb[4][R];
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) {
+                            xa[q] = atile[(4 * q + g) * 17 + sl];
+#pragma unroll
+                            for (int rj = 0; rj < R; ++rj) wb[q][rj] = wrow[(4 * q + g) * XROW + 16 * rj + sl];
+                        }
+                        const float ber[4] = {be.x, be.y, be.z, be.w};
+                        float gm[4];
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            gm[v] = live && 16 * w + 4 * g + v < N ? x[v] * ber[v] : 0.0f;
+                            lane_nan |= !__builtin_isfinite(gm[v]);
+                            if (s == 0) gpi[v] = gm[v];
+                        }
+                        // adds of one symbol's slots in rounds of their rank; the products cover
+                        // the latency of the first round's read
+                        float4 *at = (float4 *)&nbl[ot * NP + ((16 * w + 4 * g) ^ (ot * 4 & swz))];
+                        auto add = [&](float4 q) {
+                            q.x += gm[0];
+                            q.y += gm[1];
+                            q.z += gm[2];
+                            q.w += gm[3];
+                            *at = q;
+                        };
+                        const float4 q0 = *at;
+                        __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)
+#pragma unroll
+                            for (int rj = 0; rj < R; ++rj)
+                                C[rj] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[q], wb[q][rj], C[rj], 0, 0, 0);
+                        if (live && rank == 0) add(q0);
+                        for (int r = 1; __ballot(live && rank >= r) != 0; ++r) {
+                            wave_lds_sync();
+                            if (live && rank == r) add(*at);
+                        }
+                        lds_barrier();
+                    };
+                    // (the phase of step Tmax - 1 has no step to take; without a branch around a phase's
+                    // loads the wait for a row leaves the next one in flight)
+                    float4 al0 = load_row(Tmax - 1), al1 = load_row(Tmax - 2);
+                    o_next = entry(Tmax - 1, 0);
+                    advance(Tmax - 1);
+                    lds_barrier();
+                    int t = Tmax - 2;
+                    for (; t >= 0; t -= 2) {
+                        phase(t, al0);
+                        phase(t - 1, al1);
+                    }
+                    if (t == -1) phase(-1, al0);
+                    if (rank_has_prev) ranktab[rank_prev >> 1] = 0u;  // the last step (t = 0) used half 0
+                    // this tile's initial counts and n_A = A o C for this wave's rows (row base
+                    // opaque: the flush's addresses are formed here, not kept live across the loop)
+                    const int rbk = opaque(k * N + 16 * w + 4 * g);
+#pragma unroll
+                    for (int v = 0; v < 4; ++v)
+                        if (16 * w + 4 * g + v < N) add_fixed_slots(&a.pi64[rbk + v], gpi[v], F, &a.nanflag[k], sl);
+#pragma unroll
+                    for (int rj = 0; rj < R; ++rj)
+#pragma unroll
+                        for (int v = 0; v < 4; ++v) {
+                            const int jj = 16 * rj + sl;
+                            const size_t e = (size_t)(rbk + v) * N + jj;
+                            if (16 * w + 4 * g + v < N && jj < N) add_fixed(&a.A64[e], d.A[e] * C[rj][v], F, &a.nanflag[k]);
+                        }
+                    if (lane_nan) atomicOr(&a.nanflag[k], 1);
+                }
+            }  // Tmax > 0
+            // the tile's emission partial into its slab slot (zeros for an empty tile)
+            __syncthreads();
+            const int64_t slot = slab_slot(gbeg, k, tile);
+            float *dst = a.slab + (size_t)(dbg_in(slot, slab_slots(a.S, a.K), HMM_DEBUG_SLAB) ? slot : 0) * M * NP;
+            for (int idx = threadIdx.x; idx < M * NP; idx += blockDim.x) {
+                const int o = idx / NP, ic = idx % NP;
+                dst[(size_t)o * NP + (ic ^ (o * 4 & swz))] = nbl[idx];
+                nbl[idx] = 0.0f;
+            }
+        }
+    }
+}
+
 constexpr size_t COOP_LDS_LIMIT = 160 * 1024;
 
 // Dynamic LDS of the partial variant: the [M][NP] partial, then the [2][ceil(M / 2)] slot-mask table.
@@ -1089,6 +1351,35 @@ int grid_pipe(int M, int cu_count, int K) {
     }
 }
 
+// The walk over the stored rows in two parts, where its exchange rows fit beside the partial:
+// at 96 states, and at 64 where k_adj_coop would have a CU's four SIMDs to one workgroup, because
+// there are no more tiles or its partial leaves no room for a second; several of its workgroups
+// fill a CU better than the one of 8 waves and 143 registers that fits (16000 sequences of
+// 100-900 on 100 symbols, 6 models: 2.6 and 3.4 ms).  At 128 states 16 waves leave 128 registers,
+// and the step spills (3000 sequences, 100 symbols: 3.9 and 4.5 ms).
+template <int R>
+bool use_duo(int M, int S, int K, int cu_count) {
+    if (R > 6 || nb_lds_bytes<R>(M) + AdjDuoShape<R>::static_bytes > COOP_LDS_LIMIT) return false;
+    if (R == 6) return true;
+    constexpr size_t other = (AdjCoopShape<R, 1>::w_floats + AdjCoopShape<R, 1>::at_floats) * 4;
+    return tile_bound(S, K, false, TILE) <= cu_count + K || 2 * (nb_lds_bytes<R>(M) + other) > COOP_LDS_LIMIT;
+}
+
+template <int R>
+hipError_t launch_duo(const DevPtrs &d, const AdjLaunch &a, int cu_count, hipStream_t st) {
+    auto kern = k_adj_duo<R>;
+    const size_t dyn = nb_lds_bytes<R>(a.M);
+    (void)hipFuncSetAttribute((const void *)kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)dyn);
+    int per_cu = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, 2 * R * WAVE, dyn) != hipSuccess || per_cu < 1)
+        per_cu = 1;
+    int full = cu_count * per_cu;
+    if (a.K > 0 && full >= a.K) full = full / a.K * a.K;
+    const int grid = persistent_grid(full, tile_bound(a.S, a.K, false, TILE), 1, a.K, a.max_grid);
+    kern<<<grid, 2 * R * WAVE, dyn, st>>>(d, a);
+    return hipGetLastError();
+}
+
 template <int R, bool NBLDS, bool FULL = false>
 int grid_t(int M, int cu_count, int K) {
     constexpr int BO = adj_bo(R);
@@ -1127,7 +1418,12 @@ hipError_t launch_r(const DevPtrs &d, const AdjLaunch &a, int cu_count, hipStrea
         if (slab_shape && (STREAM || a.slab == nullptr)) return hipErrorInvalidValue;
         if (!slab_shape && a.B64 == nullptr) return hipErrorInvalidValue;
         if constexpr (!STREAM) {
-            if (slab_shape) {
+            if (slab_shape && use_duo<R>(a.M, a.S, a.K, cu_count)) {
+                if constexpr (R <= 6) {
+                    const hipError_t e = launch_duo<R>(d, a, cu_count, st);
+                    if (e != hipSuccess) return e;
+                }
+            } else if (slab_shape) {
                 const int gf = persistent_grid(grid_t<R, true, true>(a.M, cu_count, a.K), tile_bound(a.S, a.K, false, TILE),
                                                1, a.K, a.max_grid);
                 k_adj_coop<R, BO, true, false, true><<<gf, R / BO * WAVE, nb_lds_bytes<R>(a.M), st>>>(d, a);
