@@ -76,13 +76,14 @@ FAMILY_KERNELS = {
 }
 # The kernels whose HBM traffic profiles/traffic.json records, by workload: the
 # kernel as rocprofv3 names it and the files its code comes from.
-_FWD_COOP = ["paper_1310_3322_amd/csrc/fwd_coop.hip", "paper_1310_3322_amd/csrc/coop_step.cuh"] + _COMMON
+_FWD_COOP = ["paper_1310_3322_amd/csrc/fwd_coop.hip", "paper_1310_3322_amd/csrc/coop_step.cuh",
+             "paper_1310_3322_amd/csrc/split3.cuh"] + _COMMON
 _ADJ_COOP = ["paper_1310_3322_amd/csrc/adj_coop.hip", "paper_1310_3322_amd/csrc/coop_step.cuh"] + _COMMON
 TRAFFIC_KERNELS = {
     "c3_classify": ("k_fwd_mfma32<1, true>", FAMILY_KERNELS["tile32"][2]),
     "c4_grad_forward": ("k_fwd_coop<4, 1, true>", _FWD_COOP),
     "c4_grad_adjoint": ("k_adj_pipe<4>", _ADJ_COOP),
-    "c5_forward": ("k_fwd_coop<16, 2, false>", _FWD_COOP),
+    "c5_forward": ("k_fwd_coop<16, 4, false>", _FWD_COOP),
     "c5_grad_forward": ("k_fwd_coop<16, 2, true>", _FWD_COOP),
     "c5_grad_adjoint": ("k_adj_coop<16, 2, false, true, true>", _ADJ_COOP),
     "c5_grad_counts": ("k_grows_reduce", _ADJ_COOP),
