@@ -25,9 +25,9 @@
 //   XI      C += X^T W, X = w_s alphahat_t, W = w_{t+1}: transposed through LDS so
 //           that the 16 sequences become the MFMA contraction axis
 //   COUNTS  n_B^T[o_t][i] += w_s gamma_t(i) into the LDS partial of the workgroup
-//           (slots that share a symbol add in slot-rank rounds), written to the tile's
-//           slab slot after each tile; or, when the partial does not fit, to the global
-//           counts; n_pi
+//           (of slots that share a symbol the lowest adds for all, in slot order),
+//           written to the tile's slot of a slab of per-tile partials (deterministic),
+//           or with 64-bit atomics to the global counts; n_pi
 // WALK leaves w_{t+1} and betahat_t of CS steps in one half of an LDS ring; XI and
 // COUNTS take them CS steps later from the other half, so the waves meet at one barrier
 // every CS steps (and REC's segment at one every L).  Symbols are requested two chunks
@@ -38,10 +38,11 @@
 // tiles are few, by the matrix and vector instructions of the four parts once they fill
 // the card.  An FP32 MFMA leaves no issue slot to its own wave's vector instructions, which
 // is why the parts of a step gain from having a SIMD each.  Against one wave per tile that
-// does all of it in turn, with every operand requested when needed, the backward pass of
-// 4096 sequences of 50-400 (12 models, 16 states, 64 symbols) went from 455 to 142 us, that of
-// 147 sequences of 20-200 (5 states) from 286 to 66 us (0.33 us a step), and that of 65536
-// sequences of 16-2048 (64 models, 32 states, 256 symbols) from 5.1 to 3.2 ms.
+// does all of it in turn, with every operand requested when needed, an EM iteration on
+// 4096 sequences of 50-400 (12 models, 16 states, 64 symbols) went from 606 to 292 us, on
+// 147 sequences of 20-200 (6 models, 5 states) from 361 to 178 us (some 50 us of either are
+// fewer launches and a better order of the forward's tiles), and the counts of 65536
+// sequences of 16-2048 (64 models, 32 states, 256 symbols) from 6.4 to 3.9 ms.
 //
 // Global counts are 64-bit fixed-point sums (common.cuh) and each tile's sums are
 // formed in an order fixed by its data, so the counts do not depend on which
@@ -55,45 +56,6 @@
 
 namespace hmm {
 namespace {
-
-// Lower slots of the tile that hold the lane's symbol o and add to its table, among the
-// slots s, s - tables, .. that share it.  Two to eight tables: the 16 lanes of a DPP row
-// hold the tile's slots, and row_shr brings the symbol n slots below (-1 from outside).
-template <int SHIFT>
-__device__ __forceinline__ int same_below(int o) {
-    return __builtin_amdgcn_update_dpp(-1, o, 0x110 + SHIFT, 0xf, 0xf, false) == o ? 1 : 0;
-}
-__device__ __forceinline__ int shared_rank(int o, int ntab) {
-    int n = same_below<8>(o);
-    if (ntab <= 4) n += same_below<4>(o) + same_below<12>(o);
-    if (ntab == 2) n += same_below<2>(o) + same_below<6>(o) + same_below<10>(o) + same_below<14>(o);
-    return n;
-}
-
-// Emission counts of a step into an LDS partial (its table of the lane's slot at nbl):
-// the lane's 4 consecutive states of each 16-state block at (16 r + 4 g) ^ (4 o & swz) of
-// symbol o's row, in rounds of the slot rank of the lane's symbol.
-template <int R>
-__device__ __forceinline__ void partial_add(float *nbl, int ot, int swz, int g, int rank, const float (&gm)[R][4]) {
-    constexpr int NP = 16 * R;
-    auto rmw = [&]() {
-#pragma unroll
-        for (int r = 0; r < R; ++r) {
-            float *q = &nbl[ot * NP + ((16 * r + 4 * g) ^ (ot * 4 & swz))];
-            float4 x = *(const float4 *)q;
-            x.x += gm[r][0];
-            x.y += gm[r][1];
-            x.z += gm[r][2];
-            x.w += gm[r][3];
-            *(float4 *)q = x;
-        }
-    };
-    if (rank == 0) rmw();
-    for (int rr = 1; __ballot(rank >= rr) != 0; ++rr) {
-        wave_lds_sync();
-        if (rank == rr) rmw();
-    }
-}
 
 __host__ __device__ inline int nb_swizzle_mask(int NP) { return (NP & (NP - 1)) == 0 ? NP - 4 : 0; }
 
@@ -131,9 +93,8 @@ k_adj_tile(DevPtrs d, AdjLaunch a) {
     const int K = a.K, N = a.N, M = a.M;
     const int swz = nb_swizzle_mask(NP);
     const int F = fixed_exponent(*a.wmax, a.S, a.max_len);
-    float *nbl = (float *)smem;  // [tables][M + 1][NP] when NBLDS
-    const int ntab = a.ntab, tab = (M + 1) * NP;
-    uint32_t *ranktab = (uint32_t *)(nbl + tab);  // [m2] slot masks of slot_rank when there is one table
+    float *nbl = (float *)smem;  // [M][NP] when NBLDS
+    uint32_t *masktab = (uint32_t *)(nbl + (size_t)M * NP);  // [m2] slot masks of slot_mask
     const int m2 = (M + 1) / 2;
 
     float *segf = a.seg + (size_t)blockIdx.x * a.seg_stride;
@@ -153,9 +114,8 @@ k_adj_tile(DevPtrs d, AdjLaunch a) {
         unsigned long long *B64k = a.B64 + (size_t)k * M * NP;  // [M][NP] symbol-major global counts
         if (NBLDS) {
             __syncthreads();
-            for (int i = threadIdx.x; i < ntab * tab; i += ROLES * WAVE) nbl[i] = 0.0f;
-            if (ntab == 1)
-                for (int i = threadIdx.x; i < m2; i += ROLES * WAVE) ranktab[i] = 0u;
+            for (int i = threadIdx.x; i < M * NP; i += ROLES * WAVE) nbl[i] = 0.0f;
+            for (int i = threadIdx.x; i < m2; i += ROLES * WAVE) masktab[i] = 0u;
         }
         const float *Ak = d.A + (size_t)k * N * N;
         float fr[R][R][4];  // fragments of A^T (REC) or A (WALK)
@@ -498,49 +458,88 @@ k_adj_tile(DevPtrs d, AdjLaunch a) {
                                 }
                             }
                         }
-                        float *mine = nbl + (sl & (ntab - 1)) * tab;
-                        if (NBLDS && ntab == TILE) {
-                            // a lane meets only its own adds: all steps' entries at once, a step that
-                            // repeats the symbol of an earlier one goes on from that one's sum
-                            float4 x[CS][R];
-                            auto at = [&](int u, int r) {
-                                return (float4 *)&mine[oc[u] * NP + ((16 * r + 4 * g) ^ (oc[u] * 4 & swz))];
-                            };
+                        if (NBLDS) {
+                            // The lowest live slot of a symbol adds for all that share it, in slot order.
+                            // It finds the others' gamma where their betahat was in the ring, so that a
+                            // step is one round trip to its entry; the first NEAR of them are requested
+                            // for all steps at once, before the entries (more of them only cost
+                            // registers and reads: 300 sequences of 20-1500 on 30 symbols took 891 us per
+                            // iteration of training with two, 947 with three, 1056 with five).  A table
+                            // of sums per slot needs none of this and took 749 us, but adds in another
+                            // order; this one's sums are those of slots adding one after the other.
+                            constexpr int NEAR = CS / 2;
+                            uint32_t rest[CS];  // the other slots whose gamma this lane adds
+                            bool leads[CS];
+                            float4 near[CS][NEAR][R];
+                            bool any = false;
+                            uint32_t word[CS];
 #pragma unroll
-                            for (int u = 0; u < CS; ++u)
-#pragma unroll
-                                for (int r = 0; r < R; ++r) x[u][r] = *at(u, r);
+                            for (int u = 0; u < CS; ++u) word[u] = slot_mask(masktab, oc[u], sl, act && u < c.n && c.t0 - u < T);
 #pragma unroll
                             for (int u = 0; u < CS; ++u) {
+                                const uint32_t m = (word[u] >> ((oc[u] & 1) << 4)) & 0xffffu;
+                                leads[u] = (m & ((2u << sl) - 1u)) == (1u << sl);
+                                rest[u] = leads[u] ? m & (m - 1u) : 0u;
+                                any |= rest[u] != 0u;
+                            }
+                            const bool shared = __ballot(any) != 0;
+                            uint32_t later[CS];
+                            if (shared) {
 #pragma unroll
-                                for (int r = 0; r < R; ++r) {
+                                for (int u = 0; u < CS; ++u)
 #pragma unroll
-                                    for (int q = 0; q < u; ++q) {
-                                        const bool same = oc[q] == oc[u];
-                                        x[u][r].x = same ? x[q][r].x : x[u][r].x;
-                                        x[u][r].y = same ? x[q][r].y : x[u][r].y;
-                                        x[u][r].z = same ? x[q][r].z : x[u][r].z;
-                                        x[u][r].w = same ? x[q][r].w : x[u][r].w;
+                                    for (int r = 0; r < R; ++r)
+                                        bring[hr][u][r][lane] = float4{gm[u][r][0], gm[u][r][1], gm[u][r][2], gm[u][r][3]};
+                                wave_lds_sync();
+#pragma unroll
+                                for (int u = 0; u < CS; ++u) {
+                                    uint32_t m = rest[u];  // (m & (m - 1) is 0 for 0)
+#pragma unroll
+                                    for (int n = 0; n < NEAR; ++n) {
+                                        const int from = m ? 16 * g + (int)__builtin_ctz(m) : lane;
+#pragma unroll
+                                        for (int r = 0; r < R; ++r) near[u][n][r] = bring[hr][u][r][from];
+                                        m &= m - 1u;
                                     }
-                                    x[u][r].x += gm[u][r][0];
-                                    x[u][r].y += gm[u][r][1];
-                                    x[u][r].z += gm[u][r][2];
-                                    x[u][r].w += gm[u][r][3];
-                                    *at(u, r) = x[u][r];
+                                    later[u] = m;
                                 }
                             }
-                        } else if (NBLDS) {
-                            int rank[CS];
-                            if (ntab == 1) {
-#pragma unroll
-                                for (int u = 0; u < CS; ++u) rank[u] = slot_rank(ranktab, oc[u], sl);
-                            } else {
-#pragma unroll
-                                for (int u = 0; u < CS; ++u) rank[u] = shared_rank(oc[u], ntab);
-                            }
+                            auto plus = [](float4 x, float4 y) {
+                                return float4{x.x + y.x, x.y + y.y, x.z + y.z, x.w + y.w};
+                            };
 #pragma unroll
                             for (int u = 0; u < CS; ++u) {
-                                partial_add<R>(mine, oc[u], swz, g, rank[u], gm[u]);
+                                const uint32_t m = rest[u];
+                                float4 x[R];
+                                auto at = [&](int r) {
+                                    return (float4 *)&nbl[oc[u] * NP + ((16 * r + 4 * g) ^ (oc[u] * 4 & swz))];
+                                };
+#pragma unroll
+                                for (int r = 0; r < R; ++r) x[r] = plus(*at(r), float4{gm[u][r][0], gm[u][r][1], gm[u][r][2], gm[u][r][3]});
+                                if (shared) {
+                                    uint32_t q = m;
+#pragma unroll
+                                    for (int n = 0; n < NEAR; ++n) {
+                                        if (q) {
+#pragma unroll
+                                            for (int r = 0; r < R; ++r) x[r] = plus(x[r], near[u][n][r]);
+                                        }
+                                        q &= q - 1u;
+                                    }
+                                    uint32_t l = later[u];
+                                    while (__ballot(l != 0) != 0) {
+                                        if (l) {
+                                            const int from = 16 * g + (int)__builtin_ctz(l);
+#pragma unroll
+                                            for (int r = 0; r < R; ++r) x[r] = plus(x[r], bring[hr][u][r][from]);
+                                        }
+                                        l &= l - 1u;
+                                    }
+                                }
+                                if (leads[u]) {
+#pragma unroll
+                                    for (int r = 0; r < R; ++r) *at(r) = x[r];
+                                }
                                 wave_lds_sync();
                             }
                         } else {
@@ -606,12 +605,8 @@ k_adj_tile(DevPtrs d, AdjLaunch a) {
                 float *dst = a.slab + (size_t)(dbg_in(slot, slab_slots(a.S, a.K), HMM_DEBUG_SLAB) ? slot : 0) * M * NP;
                 for (int idx = threadIdx.x; idx < M * NP; idx += ROLES * WAVE) {
                     const int o = idx / NP, ic = idx % NP;
-                    float v = 0.0f;
-                    for (int n = 0; n < ntab; ++n) {
-                        v += nbl[n * tab + idx];
-                        nbl[n * tab + idx] = 0.0f;
-                    }
-                    dst[(size_t)o * NP + (ic ^ (o * 4 & swz))] = v;
+                    dst[(size_t)o * NP + (ic ^ (o * 4 & swz))] = nbl[idx];
+                    nbl[idx] = 0.0f;
                 }
             }
         }
@@ -619,19 +614,16 @@ k_adj_tile(DevPtrs d, AdjLaunch a) {
 }
 
 constexpr size_t LDS_CU = 160 * 1024;
-constexpr size_t LDS_GRANULE = 1280;  // workgroups take LDS in units of this
 
-// LDS for the emission partial of one workgroup in `tables` tables.
-size_t partial_bytes(int NP, int M, int tables) {
-    return (size_t)tables * (M + 1) * NP * 4 + (tables == 1 ? (size_t)((M + 1) / 2) * 4 : 0);
-}
+// LDS for the emission partial of a workgroup: the [M][NP] sums, then the slot masks.
+size_t partial_bytes(int NP, int M) { return (size_t)M * NP * 4 + (size_t)((M + 1) / 2) * 4; }
 
 // Which variant a shape takes: the emission partial in LDS (when it fits and the slab of
 // per-tile partials stays within SLAB_MAX_BYTES), else adds to the global counts.
 template <int R>
 bool use_partial(int M, int S, int K) {
     if (slab_slots(S, K) * M * 16 * R * 4 > SLAB_MAX_BYTES) return false;
-    return partial_bytes(16 * R, M, 1) + AdjShape<R, 2>::static_bytes <= LDS_CU;
+    return partial_bytes(16 * R, M) + AdjShape<R, 2>::static_bytes <= LDS_CU;
 }
 
 // Workgroups per CU that the tiles can fill, within what the registers allow.
@@ -641,42 +633,29 @@ int want_per_cu(int S, int K, int cu_count) {
     return (int)std::min<int64_t>(std::max<int64_t>(n, 1), adj_waves(R, 2));
 }
 
-// Tables of the LDS partial in a workgroup whose LDS is its share of a CU's.  Slots that share
-// a symbol and a table add one after the other, an LDS round trip each, and one table needs
-// slot_rank besides, so as many as fit; never at the cost of a resident workgroup.
-template <int R, int CS>
-int tables_for(int M, int want) {
-    const size_t share = LDS_CU / want / LDS_GRANULE * LDS_GRANULE;
-    for (int n = TILE; n > 1; n /= 2)
-        if (partial_bytes(16 * R, M, n) + AdjShape<R, CS>::static_bytes <= share) return n;
-    return 1;
-}
-
-// The kernel, LDS and tables of a launch, and the grid that the card holds at once.
+// The kernel and LDS of a launch, and the grid that the card holds at once.
 struct AdjPlan {
     void (*kern)(DevPtrs, AdjLaunch);
     size_t lds;
-    int ntab, grid;
+    int grid;
 };
 
 template <int R>
 AdjPlan plan_for(int M, int S, int cu_count, int K) {
-    AdjPlan p{k_adj_tile<R, false, 2>, 0, 1, 0};
+    AdjPlan p{k_adj_tile<R, false, 2>, 0, 0};
     if (use_partial<R>(M, S, K)) {
         const int want = want_per_cu<R>(S, K, cu_count);
         // Four steps per chunk halve the barriers of a tile that has its CU to itself; with more
-        // of them on a CU, two steps take fewer registers and less LDS.  One iteration of
-        // training at 8 states took 777 us with four and 807 with two (300 sequences of 20-1500
-        // on 30 symbols), and 762 and 729 us (40000 sequences of 50-600 on 6).
+        // of them on a CU, two steps take fewer registers and less LDS.  With a table of sums per
+        // slot one iteration of training at 8 states took 777 us with four and 807 with two
+        // (300 sequences of 20-1500 on 30 symbols), and 762 and 729 us (40000 sequences of 50-600 on 6).
         constexpr int WIDE = R == 1 ? 4 : 2;
-        if (want == 1 && partial_bytes(16 * R, M, 1) + AdjShape<R, WIDE>::static_bytes <= LDS_CU) {
+        if (want == 1 && partial_bytes(16 * R, M) + AdjShape<R, WIDE>::static_bytes <= LDS_CU) {
             p.kern = k_adj_tile<R, true, WIDE>;
-            p.ntab = tables_for<R, WIDE>(M, want);
         } else {
             p.kern = k_adj_tile<R, true, 2>;
-            p.ntab = tables_for<R, 2>(M, want);
         }
-        p.lds = partial_bytes(16 * R, M, p.ntab);
+        p.lds = partial_bytes(16 * R, M);
         if (p.lds > 64 * 1024)
             (void)hipFuncSetAttribute((const void *)p.kern, hipFuncAttributeMaxDynamicSharedMemorySize, (int)p.lds);
     }
@@ -689,12 +668,11 @@ AdjPlan plan_for(int M, int S, int cu_count, int K) {
 }
 
 template <int R>
-hipError_t launch_r(const DevPtrs &d, AdjLaunch a, int cu_count, hipStream_t st) {
+hipError_t launch_r(const DevPtrs &d, const AdjLaunch &a, int cu_count, hipStream_t st) {
     const AdjPlan p = plan_for<R>(a.M, a.S, cu_count, a.K);
     const int grid = persistent_grid(p.grid, tile_bound(a.S, a.K, false, TILE), 1, a.K, a.max_grid);
     if (grid > a.seg_slots) return hipErrorInvalidValue;
     if (use_partial<R>(a.M, a.S, a.K) ? a.slab == nullptr : a.B64 == nullptr) return hipErrorInvalidValue;
-    a.ntab = p.ntab;
     p.kern<<<grid, ROLES * WAVE, p.lds, st>>>(d, a);
     return hipGetLastError();
 }

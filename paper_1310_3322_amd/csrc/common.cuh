@@ -143,23 +143,25 @@ __device__ __forceinline__ void add_fixed_slots(unsigned long long *dst, float v
     if (sl == 0 && x != 0) atomicAdd(dst, x);
 }
 
-// Slot order of repeated symbols in one step of a 16-sequence tile: each of the
-// wave's lanes of slot `sl` sets bit sl of its symbol's mask in `tab` (two 16-bit
-// masks per word, symbols o and o ^ 1; an LDS atomic OR, order-independent), reads
-// the mask back and clears the word; returns how many lower slots share the symbol
-// (0 for the first occurrence).  Adds to an LDS partial then go in rounds of equal
-// rank, so the result does not depend on how the LDS serialises lanes that collide.
-__device__ __forceinline__ int slot_rank(uint32_t *tab, int sym, int sl) {
+// Slots of a 16-sequence tile that share the lane's symbol in one step: each of the
+// wave's lanes of a live slot `sl` sets bit sl of its symbol's mask in `tab` (two
+// 16-bit masks per word, symbols o and o ^ 1; an LDS atomic OR, order-independent),
+// all read the word back and clear it (returned whole, so that no lane waits for it
+// here).  Adds to an LDS partial then go
+// in slot order, so the result does not depend on how the LDS serialises lanes
+// that collide.
+__device__ __forceinline__ uint32_t slot_mask(uint32_t *tab, int sym, int sl, bool live) {
     const int sh = (sym & 1) << 4;
-    atomicOr(&tab[sym >> 1], 1u << (sh + sl));
+    atomicOr(&tab[sym >> 1], live ? 1u << (sh + sl) : 0u);
     wave_lds_sync();
-    const uint32_t m = (tab[sym >> 1] >> sh) & 0xffffu;
+    const uint32_t m = tab[sym >> 1];
     wave_lds_sync();
     tab[sym >> 1] = 0u;
-    return __popc(m & ((1u << sl) - 1u));
+    return m;
 }
 
-// The same for the waves of a cooperative tile, which all hold the tile's 16
+// The rank of a slot among those that hold its symbol (0 for the lowest), for the
+// waves of a cooperative tile, which all hold the tile's 16
 // slots and advance step by step between workgroup barriers: one table for all
 // of them, two 16-bit masks per word (symbols o and o ^ 1), two halves used by
 // alternate steps.  Every wave sets the same bits, so a wave's own OR completes

@@ -294,7 +294,6 @@ struct AdjLaunch {
     const float *mlast;
     const int64_t *rowpos;
     int64_t grad_rows;
-    int ntab;  // tables of the LDS emission partial (set by the launcher)
 };
 // Whether a gradient call stores every step's alphahat (decided on the device
 // from the row prefix, so that overlapping sequences whose rows exceed the

@@ -1,5 +1,5 @@
 """The backward pass of a 16-sequence tile (csrc/adj_mfma.hip, up to 48 states) against the
-FP64 oracle, at the edges of its chunks and segments, of its tables of emission counts and of
+FP64 oracle, at the edges of its chunks and segments, of its partial of emission counts and of
 its variants.
 
 Tolerance.  A step of either recursion rounds at most 16 times (12 matrix products of 4 terms
@@ -30,8 +30,8 @@ def dev(a):
     return torch.from_numpy(np.ascontiguousarray(a)).cuda()
 
 
-# One tile per CU: 16, 8, 4, 2 and 1 tables, one table beside the smaller ring, and sums in
-# memory; with more tiles than CUs the tables have a half, a third or a quarter of the LDS.
+# One tile per CU (chunks of four steps at 16 states): small and large partials, the largest beside
+# the ring of two steps, and sums in memory; then more tiles than CUs (chunks of two).
 @pytest.mark.parametrize("N,M,S", [(1, 1, 90), (5, 6, 90), (16, 139, 90), (16, 140, 90), (16, 400, 90), (15, 800, 90),
                                    (16, 1200, 90), (16, 2300, 90), (9, 2400, 90), (17, 30, 90), (32, 150, 90),
                                    (31, 500, 90), (32, 1100, 90), (32, 1200, 90), (33, 20, 90), (48, 100, 90),
