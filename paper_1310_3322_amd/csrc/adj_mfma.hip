@@ -30,8 +30,9 @@
 //           or with 64-bit atomics to the global counts; n_pi
 // WALK leaves w_{t+1} and betahat_t of CS steps in one half of an LDS ring; XI and
 // COUNTS take them CS steps later from the other half, so the waves meet at one barrier
-// every CS steps (and REC's segment at one every L).  Symbols are requested two chunks
-// of CS steps ahead, emission rows and alphahat one chunk ahead.
+// every CS steps (and at one that orders global memory too every L, for REC's segments).
+// Symbols are requested two chunks of CS steps ahead, emission rows and alphahat one chunk
+// ahead.
 //
 // Bound by the latency of a step of WALK and REC (about the same: four dependent 16x16x4
 // MFMAs of 33 cycles and some 20 dependent vector instructions at 16 states) while the
@@ -71,6 +72,15 @@ struct AdjShape {
     // packed exponents [L][64]
     static constexpr int seg_step = WAVE * (4 * R + 1);  // floats per step
 };
+
+// The barrier between two segments for the waves that read the segment buffer.  REC writes the
+// half of segment j again in the phase after XI and COUNTS request their last rows of it, so
+// global memory is ordered here too, and no load of theirs is left in flight (they took its value
+// at the end of the phase: nothing to wait for as it is compiled now).
+__device__ __forceinline__ void segment_barrier() {
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    __syncthreads();
+}
 
 // Waves per SIMD that the registers are kept to.
 constexpr int adj_waves(int R, int CS) { return CS == 4 ? 2 : R == 1 ? 4 : R == 2 ? 3 : 2; }
@@ -292,7 +302,7 @@ k_adj_tile(DevPtrs d, AdjLaunch a) {
                         const int j = nseg - p;
                         const int LA = p > 0 ? seg_len(j) : 0;
                         const int32_t *se = seg_e(j);
-                        lds_barrier();  // (REC's barrier publishes the segment)
+                        __syncthreads();  // the segment is visible, and its exponents' half free for REC
 #pragma unroll
                         for (int u = 0; u < CS; ++u) ec[u] = elast[j & 1][u][sl];
                         for (int s = 0; s < nch; ++s, half_ring ^= 1) {
@@ -395,7 +405,7 @@ k_adj_tile(DevPtrs d, AdjLaunch a) {
                     for (int p = 0; p <= nseg; ++p) {
                         const int j = nseg - p;
                         const float4 *sa = seg_alpha(j);
-                        lds_barrier();
+                        segment_barrier();
                         for (int s = 0; s < nch; ++s, half_ring ^= 1) {
                             const Chunk cn = back_chunk(j, s);
 #pragma unroll
@@ -404,8 +414,6 @@ k_adj_tile(DevPtrs d, AdjLaunch a) {
                                 for (int r = 0; r < R; ++r)
                                     an[u][r] = sa[(size_t)(max(cn.n - 1 - u, 0) * R + r) * WAVE + lane];
                             if (cp.n > 0) take(cp, half_ring ^ 1);
-                            // (the copies wait for this chunk's loads, which thus end before REC writes
-                            // the other half again)
 #pragma unroll
                             for (int u = 0; u < CS; ++u)
 #pragma unroll
@@ -572,7 +580,7 @@ k_adj_tile(DevPtrs d, AdjLaunch a) {
                     for (int p = 0; p <= nseg; ++p) {
                         const int j = nseg - p;
                         const float4 *sa = seg_alpha(j);
-                        lds_barrier();
+                        segment_barrier();
                         for (int s = 0; s < nch; ++s, half_ring ^= 1) {
                             const Chunk cn = back_chunk(j, s);
 #pragma unroll
@@ -583,7 +591,6 @@ k_adj_tile(DevPtrs d, AdjLaunch a) {
                                 on[u] = load_sym(cn.t0 - u);
                             }
                             if (cp.n > 0) take(cp, half_ring ^ 1);
-                            // (as in XI)
 #pragma unroll
                             for (int u = 0; u < CS; ++u) {
                                 oc[u] = checked(on[u]);
