@@ -224,7 +224,8 @@ struct SplitFrags {
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
                     const int i0 = 32 * c + 16 * (j / 4) + j % 4;
-                    q[j] = (i0 + 4 * g < N && 16 * (r0 + b) + sl < N) ? Ak[lane_off + i0 * N + 16 * b] : 0.0f;
+                    const float x = (i0 + 4 * g < N && 16 * (r0 + b) + sl < N) ? Ak[lane_off + i0 * N + 16 * b] : 0.0f;
+                    q[j] = ldexp_f(x, SPLIT_SHIFT);
                 }
                 a[b][c] = split8(sc, q);
                 // Four blocks take the register file of a SIMD: 21 of the 32 fragments (252
@@ -253,7 +254,8 @@ __device__ __forceinline__ void split_read(const unsigned char *buf, int c, int 
     for (int p = 0; p < 3; ++p) q[p] = *(const bf16x8 *)(buf + p * SH::PIECE + sl * SH::ROW + 64 * c + 16 * g);
 }
 
-// u[b] = (fragments . X) 2^-e, X from the exchange buffer; q0: its chunk 0, which a caller
+// u[b] = (fragments . X) 2^-e, X from the exchange buffer, e the exponent of X's sum (the
+// fragments' 2^SPLIT_SHIFT stays in u, X's goes with its sum); q0: its chunk 0, which a caller
 // may request before it forms e.  The operands of chunk c + 1 are read while chunk c's
 // products issue; the scheduling barriers keep the compiler from hoisting every read.
 template <int R, int BO>

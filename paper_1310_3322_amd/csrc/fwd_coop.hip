@@ -141,7 +141,7 @@ __global__ void __launch_bounds__(R / BO * WAVE) k_fwd_coop(DevPtrs d, FwdLaunch
             for (int b = 0; b < BO; ++b) bA[b] = *(const float4 *)&btk[(size_t)o * NP + 16 * (r0 + b) + 4 * g];
             float x[BO][4] = {};
             int E = 0, E_end = 0;
-            float c_end = 1.0f;
+            float c_end = ldexp_f(1.0f, SPLIT ? SPLIT_SHIFT : 0);
             int ck_t = 0, ck_c = 0;  // next checkpointed step and its index
             // Read phase of step t: finishes step t - 1 (its sum, exponent and
             // checkpoint) and returns that step's exponent (0 at t = 0).
@@ -232,7 +232,7 @@ __global__ void __launch_bounds__(R / BO * WAVE) k_fwd_coop(DevPtrs d, FwdLaunch
 #pragma unroll
                         for (int v = 0; v < 4; ++v) {
                             const int i = 16 * (r0 + b) + 4 * g + v;
-                            u[b][v] = i < N ? pik[i] : 0.0f;
+                            u[b][v] = i < N ? ldexp_f(pik[i], SPLIT ? SPLIT_SHIFT : 0) : 0.0f;
                         }
                 } else {
                     if constexpr (SPLIT)
@@ -271,6 +271,10 @@ __global__ void __launch_bounds__(R / BO * WAVE) k_fwd_coop(DevPtrs d, FwdLaunch
             }
             if (t < Tmax) step(t++, bA, AHEAD ? bB : bA, AHEAD ? oB : oA, AHEAD ? oA : oB, false, false);
             read_phase(t);
+            if constexpr (SPLIT) {  // each step's sum held 2^SPLIT_SHIFT
+                E_end -= SPLIT_SHIFT * max(T - 1, 0);
+                c_end = ldexp_f(c_end, -SPLIT_SHIFT);
+            }
             if (has && g == 0 && w == 0) {
                 float r = (float)((double)E_end * LN2 + (double)logf(c_end));
                 if (bad || symbad) r = NAN;
