@@ -125,7 +125,10 @@ size_t hmm_workspace_size(const hmm_bank *bank, const hmm_batch *batch, int op);
 
 /* Forward log-likelihoods (Sec. 2.7 "Forward"; Sec. 3 item 3).
  * loglik: [S][K] (sequence-major) when batch->model_of_seq == NULL, else [S];
- * natural log, FP32. */
+ * natural log, FP32.  Above 48 states a sequence's value under its own model
+ * (the [S] form) may be formed from split products and then agrees with its entry
+ * of the [S][K] table, and with the gradient's loglik, to rounding, not bit for
+ * bit; the table is FP32 throughout, as hmm_classify's is. */
 hmm_status hmm_forward_loglik(const hmm_bank *bank, const hmm_batch *batch, float *loglik,
                               void *ws, size_t ws_bytes, hipStream_t stream);
 

@@ -6,13 +6,21 @@
 // workgroup of R / BO waves (R = NP / 16 state blocks, BO blocks per wave) per
 // tile of 16 length-sorted sequences of one model (see coop_step.cuh for the
 // data movement).  Per step and workgroup: 3 R^2 bf16 MFMAs of 16x16x32 (FP32 products
-// by three-way splits, split3.cuh; the gradient's variant keeps 4 R^2 MFMAs of 16x16x4
-// FP32), one barrier, one exchange of the tile's alpha through LDS.  Bound by the power
-// the matrix cores draw: with 256 states the clock falls to 2.1 GHz and the products run
-// at 1.4 PFLOP/s of bf16, and interleaving the epilogue with them (which filled the idle
-// vector slots) changed nothing.  16 models of 256 states, 16384 sequences of 256-4096
-// steps: 38.5 ms in FP32, 20.0 ms split; 5 models of 100 states, 1001 sequences against
-// all: 0.861 -> 0.544 ms.  Emission rows B^T[o][.] come from L2 (B^T of one model is up
+// by three-way splits, split3.cuh) where each sequence is scored under its own model, else
+// 4 R^2 MFMAs of 16x16x4 FP32; one barrier, one exchange of the tile's alpha through LDS.
+//
+// FP32 where every sequence meets every model, because recognition compares the results: the
+// splits are no less exact, but where two models' likelihoods are a rounding apart they can
+// order them the other way (4 labels of 13 million: 64 models of 66 and 100 states, sequences
+// of 4-128 steps).  And FP32 in the gradient's variant, whose backward pass repeats the step.
+//
+// The split step is bound by the power the matrix cores draw: with 256 states the clock falls
+// to 2.1 GHz and the products run at 1.4 PFLOP/s of bf16, and interleaving the epilogue with
+// them (which filled the idle vector slots) changed nothing.  FP32 and split: 16 models of 256
+// states, 16384 sequences of 256-4096 steps 38.5 and 20.1 ms; 8 models, 4096 sequences of
+// 100-800 steps, 300 symbols: 0.42 and 0.38 ms with 64 states, 0.98 and 0.62 with 100, 2.13 and
+// 1.06 with 150, 2.51 and 1.20 with 192, 2.91 and 1.47 with 224 (12, 14 and 16 blocks in
+// pieces spill 19, 40 and 26 registers, some of them reloaded in every step).  Emission rows B^T[o][.] come from L2 (B^T of one model is up
 // to 1 MiB and stays resident in its XCD's L2); the symbol and row of step t+1
 // are fetched during step t.  The gradient's variant (CKPT) keeps alphahat for
 // the backward pass: every step's row and exponent when the workspace's rows
@@ -29,11 +37,11 @@ namespace {
 
 constexpr int CCH = 32;  // symbols per staging chunk
 
-template <int R, int BO, bool CKPT>
+template <int R, int BO, bool CKPT, bool SPLIT>
 __global__ void __launch_bounds__(R / BO * WAVE) k_fwd_coop(DevPtrs d, FwdLaunch f) {
+    static_assert(!(CKPT && SPLIT), "the backward pass recomputes the FP32 step");
     using SH = CoopShape<R>;
     using SP = SplitShape<R>;
-    constexpr bool SPLIT = !CKPT;
     constexpr int NP = SH::NP;
     constexpr int XROW = SH::XROW;
     __shared__ __align__(16) float xch[SPLIT ? 1 : SH::floats];
@@ -288,16 +296,16 @@ __global__ void __launch_bounds__(R / BO * WAVE) k_fwd_coop(DevPtrs d, FwdLaunch
 }
 
 // Blocks per wave: one up to 8 blocks (N <= 128), two above, so that a lane's
-// fragments (6 R BO registers in pieces) fit the register budget of the workgroup size;
-// four at 256 states (384 of the 512 registers of a lane that has its SIMD to itself: with
-// two blocks in eight waves the fragments alone take 192 of 256).
-template <int R, bool CKPT>
-constexpr int coop_bo() { return R == 16 && !CKPT ? 4 : R > 8 ? 2 : 1; }
+// fragments (4 R BO registers, 6 R BO in pieces) fit the register budget of the workgroup size;
+// four at 256 states in pieces (384 of the 512 registers of a lane that has its SIMD to itself:
+// with two blocks in eight waves the fragments alone take 192 of 256).
+template <int R, bool SPLIT>
+constexpr int coop_bo() { return R == 16 && SPLIT ? 4 : R > 8 ? 2 : 1; }
 
-template <int R, bool CKPT>
+template <int R, bool CKPT, bool SPLIT>
 hipError_t launch_t(const DevPtrs &d, const FwdLaunch &f, int cu_count, hipStream_t st) {
-    constexpr int BO = coop_bo<R, CKPT>();
-    auto kern = k_fwd_coop<R, BO, CKPT>;
+    constexpr int BO = coop_bo<R, SPLIT>();
+    auto kern = k_fwd_coop<R, BO, CKPT, SPLIT>;
     int per_cu = 0;
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, R / BO * WAVE, 0);
     if (e != hipSuccess) return e;
@@ -307,27 +315,27 @@ hipError_t launch_t(const DevPtrs &d, const FwdLaunch &f, int cu_count, hipStrea
     return hipGetLastError();
 }
 
+template <int R>
+hipError_t launch_r(const DevPtrs &d, const FwdLaunch &f, int cu_count, hipStream_t st) {
+    if (f.ckpt != nullptr) return launch_t<R, true, false>(d, f, cu_count, st);
+    return f.all_pairs ? launch_t<R, false, false>(d, f, cu_count, st) : launch_t<R, false, true>(d, f, cu_count, st);
+}
+
 }  // namespace
 
 bool fwd_coop_supported(int NP) { return NP >= 64 && NP <= 256 && NP % 32 == 0; }
 
 hipError_t launch_fwd_coop(const DevPtrs &d, const FwdLaunch &f, int cu_count, hipStream_t st) {
-    const bool ck = f.ckpt != nullptr;
-#define HMM_COOP_CASE(R) \
-    case R:              \
-        return ck ? launch_t<R, true>(d, f, cu_count, st) : launch_t<R, false>(d, f, cu_count, st);
     switch (f.NP / 16) {
-        HMM_COOP_CASE(4)
-        HMM_COOP_CASE(6)
-        HMM_COOP_CASE(8)
-        HMM_COOP_CASE(10)
-        HMM_COOP_CASE(12)
-        HMM_COOP_CASE(14)
-        HMM_COOP_CASE(16)
-        default:
-            return hipErrorInvalidValue;
+        case 4: return launch_r<4>(d, f, cu_count, st);
+        case 6: return launch_r<6>(d, f, cu_count, st);
+        case 8: return launch_r<8>(d, f, cu_count, st);
+        case 10: return launch_r<10>(d, f, cu_count, st);
+        case 12: return launch_r<12>(d, f, cu_count, st);
+        case 14: return launch_r<14>(d, f, cu_count, st);
+        case 16: return launch_r<16>(d, f, cu_count, st);
+        default: return hipErrorInvalidValue;
     }
-#undef HMM_COOP_CASE
 }
 
 HMM_DEBUG_TAKE(debug_take_fwd_coop)
