@@ -526,12 +526,15 @@ __device__ __forceinline__ void finish_b(const AdjLaunch &a, int slab, float *cn
     if (i < N && o < M) dst[(size_t)i * M + o] = bad ? __builtin_nanf("") : tile[f % 8][f / 8];
 }
 
-// cnt_pi [K][N] and cnt_A [K][N][N] from their fixed-point sums (the first pa_blocks), and cnt_B
-// (the others), in one launch.
-__global__ void __launch_bounds__(256) k_counts_finish(AdjLaunch a, int pa_blocks, int slab, float *cnt_pi, float *cnt_A,
-                                                       float *cnt_B) {
+// cnt_pi [K][N] and cnt_A [K][N][N] from their fixed-point sums (the first pa_blocks), and the
+// b_tiles tiles of cnt_B (the others), in one launch.
+__global__ void __launch_bounds__(256) k_counts_finish(AdjLaunch a, int pa_blocks, int b_tiles, int slab, float *cnt_pi,
+                                                       float *cnt_A, float *cnt_B) {
     if ((int)blockIdx.x >= pa_blocks) {
-        finish_b(a, slab, cnt_B, (int)blockIdx.x - pa_blocks);
+        for (int blk = (int)blockIdx.x - pa_blocks; blk < b_tiles; blk += (int)gridDim.x - pa_blocks) {
+            finish_b(a, slab, cnt_B, blk);
+            __syncthreads();
+        }
         return;
     }
     const int N = a.N, K = a.K;
@@ -878,9 +881,12 @@ void launch_counts_finish(const AdjLaunch &a, bool slab, float *cnt_pi, float *c
     const int64_t n = (int64_t)a.K * a.N * (1 + a.N);
     int nb = blocks_for(n, 256);
     if (nb > 8192) nb = 8192;
-    const int64_t b_blocks = (int64_t)((a.N + 31) / 32) * ((a.M + 7) / 8) * a.K;
-    hipLaunchKernelGGL(k_counts_finish, dim3((unsigned)(nb + b_blocks)), dim3(256), 0, st, a, nb, slab ? 1 : 0, cnt_pi, cnt_A,
-                       cnt_B);
+    // (a block per tile of n_B up to 2^20 of them: a launch holds fewer than 2^32 threads, which 2^24
+    // tiles, counts of 17 GB, would reach)
+    const int64_t b_tiles = (int64_t)((a.N + 31) / 32) * ((a.M + 7) / 8) * a.K;
+    const int b_blocks = (int)std::min<int64_t>(b_tiles, 1 << 20);
+    hipLaunchKernelGGL(k_counts_finish, dim3(nb + b_blocks), dim3(256), 0, st, a, nb, (int)b_tiles, slab ? 1 : 0, cnt_pi,
+                       cnt_A, cnt_B);
 }
 
 void launch_grad_init(const AdjLaunch &a, uint32_t *wmax, hipStream_t st) {
