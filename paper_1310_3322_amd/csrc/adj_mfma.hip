@@ -470,11 +470,12 @@ k_adj_tile(DevPtrs d, AdjLaunch a) {
                             // The lowest live slot of a symbol adds for all that share it, in slot order.
                             // It finds the others' gamma where their betahat was in the ring, so that a
                             // step is one round trip to its entry; the first NEAR of them are requested
-                            // for all steps at once, before the entries (more of them only cost
-                            // registers and reads: 300 sequences of 20-1500 on 30 symbols took 891 us per
-                            // iteration of training with two, 947 with three, 1056 with five).  A table
-                            // of sums per slot needs none of this and took 749 us, but adds in another
-                            // order; this one's sums are those of slots adding one after the other.
+                            // for all steps at once, before the entries.  More of them cost registers and
+                            // reads, fewer a round trip each: an EM iteration with one, two, three of them
+                            // took 1130, 1083, 1051 us where symbols are often shared (8 states, 6 symbols,
+                            // 300 sequences of 20-1500), 880, 890, 948 on 30 symbols, 261, 273, 290 on 64 (12
+                            // models of 16 states, 2000 sequences of 50-400); in chunks of two 284, 296,
+                            // 306 on 64 symbols (4096 sequences) and 960, 942, 918 on 6 (40000 of 50-600).
                             constexpr int NEAR = CS / 2;
                             uint32_t rest[CS];  // the other slots whose gamma this lane adds
                             bool leads[CS];
@@ -626,7 +627,11 @@ constexpr size_t LDS_CU = 160 * 1024;
 size_t partial_bytes(int NP, int M) { return (size_t)M * NP * 4 + (size_t)((M + 1) / 2) * 4; }
 
 // Which variant a shape takes: the emission partial in LDS (when it fits and the slab of
-// per-tile partials stays within SLAB_MAX_BYTES), else adds to the global counts.
+// per-tile partials stays within SLAB_MAX_BYTES), else adds to the global counts.  Beside the
+// rings it fits up to 2317 symbols at 16 states, 1105 at 32 and 692 at 48.  Counts of 4 models, 300
+// sequences of 50-800 and 8000 of 20-300, last shape in LDS and first in memory: 16 states 468
+// and 643 us, 254 and 399; 32 states 792 and 1030, 415 and 793; 48 states 1336 and 1518, 669 and
+// 1135.
 template <int R>
 bool use_partial(int M, int S, int K) {
     if (slab_slots(S, K) * M * 16 * R * 4 > SLAB_MAX_BYTES) return false;
@@ -652,10 +657,12 @@ AdjPlan plan_for(int M, int S, int cu_count, int K) {
     AdjPlan p{k_adj_tile<R, false, 2>, 0, 0};
     if (use_partial<R>(M, S, K)) {
         const int want = want_per_cu<R>(S, K, cu_count);
-        // Four steps per chunk halve the barriers of a tile that has its CU to itself; with more
-        // of them on a CU, two steps take fewer registers and less LDS.  With a table of sums per
-        // slot one iteration of training at 8 states took 777 us with four and 807 with two
-        // (300 sequences of 20-1500 on 30 symbols), and 762 and 729 us (40000 sequences of 50-600 on 6).
+        // Four steps per chunk halve the barriers of a tile that has its CU to itself: with four
+        // and two, 174 and 184 us for an EM iteration on 147 sequences of 20-200 (6 models, 5 states),
+        // 890 and 924 on 300 of 20-1500 (8 states, 30 symbols), 273 and 272 on 2000 of 50-400 (12
+        // models, 16 states).  With more of them on a CU two steps take fewer registers and less LDS:
+        // 1361 and 962 us (40000 sequences of 50-600, 8 states, 6 symbols), 1005 and 733 (16
+        // states, 64 symbols), 295 and 284 (4096 of 50-400).
         constexpr int WIDE = R == 1 ? 4 : 2;
         if (want == 1 && partial_bytes(16 * R, M) + AdjShape<R, WIDE>::static_bytes <= LDS_CU) {
             p.kern = k_adj_tile<R, true, WIDE>;
