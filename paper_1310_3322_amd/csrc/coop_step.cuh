@@ -224,9 +224,11 @@ struct SplitFrags {
 #pragma unroll
                 for (int j = 0; j < 8; ++j) {
                     const int i0 = 32 * c + 16 * (j / 4) + j % 4;
-                    const float x = (i0 + 4 * g < N && 16 * (r0 + b) + sl < N) ? Ak[lane_off + i0 * N + 16 * b] : 0.0f;
-                    q[j] = ldexp_f(x, SPLIT_SHIFT);
+                    q[j] = (i0 + 4 * g < N && 16 * (r0 + b) + sl < N) ? Ak[lane_off + i0 * N + 16 * b] : 0.0f;
                 }
+                // (kept out of the branches around the loads, where each would wait for its load)
+#pragma unroll
+                for (int j = 0; j < 8; ++j) q[j] = ldexp_f(__int_as_float(opaque(__float_as_int(q[j]))), SPLIT_SHIFT);
                 a[b][c] = split8(sc, q);
                 // Four blocks take the register file of a SIMD: 21 of the 32 fragments (252
                 // registers) are put into accumulation registers here, where the matrix
