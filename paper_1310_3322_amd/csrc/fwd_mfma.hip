@@ -88,9 +88,20 @@ __global__ void __launch_bounds__(FWD_WAVES * WAVE) k_fwd_mfma(DevPtrs d, FwdLau
         load_fwd_fragments<R>(af, d.A + (size_t)k * N * N, N, g, sl);
         const float *pik = d.pi + (size_t)k * N;
 
-        // the first tile by the workgroup's rank, further ones from the queue
-        const int first = first_rank(G >= K ? (int)(blockIdx.x / K) : 0, f.nwg, f.turn) * FWD_WAVES + wave;
-        for (int tile = first; tile < ntiles; tile = f.nwg * FWD_WAVES + wave_pop(&f.queue[k])) {
+        // The first tile by the workgroup's rank, further ones from the queue.  (The pop at the top of
+        // the loop: at its end it cost registers and, at 16 states, the fifth wave of a SIMD, with
+        // which the grid holds two workgroups for each of 600 models instead of one; recognition of
+        // 3000 sequences of 5-40 under them took 673 us, 475 this way.  With the pop at the end and 96
+        // registers asked for by an attribute the step is slower: 16384 sequences of 1-2000 under one
+        // model 416 us, 396 this way.)
+        const int ranked = f.nwg * FWD_WAVES;  // tiles taken by rank
+        int next = first_rank(G >= K ? (int)(blockIdx.x / K) : 0, f.nwg, f.turn) * FWD_WAVES + wave - ranked;
+        for (;;) {
+            int tile = next;
+            if (tile >= 0) tile = wave_pop(&f.queue[k]);
+            tile += ranked;
+            next = 0;
+            if (tile >= ntiles) break;
             set_tile_priority(tile / FWD_WAVES / f.turn);
             const int pos = gbeg + tile * TILE + sl;
             const bool has = pos < gend;
@@ -268,7 +279,7 @@ hipError_t launch_t(const DevPtrs &d, FwdLaunch f, int cu_count, hipStream_t st)
     int per_cu = 0;
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, FWD_WAVES * WAVE, lds);
     if (e != hipSuccess) return e;
-    if (per_cu < 1) per_cu = 1;
+    per_cu = ranked_per_cu(per_cu, lds + FWD_WAVES * SYM_INTS * sizeof(int32_t), cu_count, f.K);
     const int grid = persistent_grid(cu_count * per_cu, tile_bound(f.S, f.K, f.all_pairs, TILE), FWD_WAVES, f.K, f.max_grid);
     f.nwg = grid >= f.K ? grid / f.K : 1;
     f.turn = std::max(cu_count / f.K, 1);

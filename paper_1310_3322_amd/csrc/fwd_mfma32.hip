@@ -111,11 +111,17 @@ k_fwd_mfma32(DevPtrs d, FwdLaunch f) {
         // the first tile by the workgroup's rank in its slice, further ones from the queue (one
         // queue for all took 603 us for 12 models x 8192 sequences of 50-400 at 32 states, 704
         // for sequences of one length, and 2100 for 65536 of 50-2000 each under one of 64 models;
-        // this 426, 518 and 1400)
+        // this 426, 518 and 1400; the pop at the top of the loop spills the fewest registers)
         // (a slice of the grid need not be a multiple of K)
         const int nwg = G >= K ? (G - k + K - 1) / K : 1;
-        const int first = first_rank(G >= K ? gi / K : 0, nwg, max(f.turn / XS, 1)) * WAVES32 + wave;
-        for (int jt = first; jt < ntiles; jt = nwg * WAVES32 + wave_pop(&f.queue[k * XS + x])) {
+        const int ranked = nwg * WAVES32;  // tiles taken by rank
+        int next = first_rank(G >= K ? gi / K : 0, nwg, max(f.turn / XS, 1)) * WAVES32 + wave - ranked;
+        for (;;) {
+            int jt = next;
+            if (jt >= 0) jt = wave_pop(&f.queue[k * XS + x]);
+            jt += ranked;
+            next = 0;
+            if (jt >= ntiles) break;
             const int tile = XS * jt + ((jt & 1) ? XS - 1 - x : x);
 
             const int pos = gbeg + tile * T32 + sl;
@@ -316,7 +322,7 @@ hipError_t launch_t(const DevPtrs &d, FwdLaunch f, int cu_count, hipStream_t st)
     int per_cu = 0;
     hipError_t e = hipOccupancyMaxActiveBlocksPerMultiprocessor(&per_cu, kern, WAVES32 * WAVE, lds);
     if (e != hipSuccess) return e;
-    if (per_cu < 1) per_cu = 1;
+    per_cu = ranked_per_cu(per_cu, lds + WAVES32 * SYM32 * (BLDS ? sizeof(uint16_t) : sizeof(int32_t)), cu_count, f.K);
     const int grid = persistent_grid(cu_count * per_cu, tile_bound(f.S, f.K, f.all_pairs, T32), WAVES32, f.K, f.max_grid);
     f.turn = std::max(cu_count / f.K, 1);
     hipLaunchKernelGGL(kern, dim3(grid), dim3(WAVES32 * WAVE), lds, st, d, f);

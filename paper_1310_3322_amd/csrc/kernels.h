@@ -5,6 +5,8 @@
 #include <stddef.h>
 #include <stdint.h>
 
+#include <algorithm>
+
 #include "common.cuh"
 
 namespace hmm {
@@ -77,6 +79,21 @@ inline int persistent_grid(int occ_grid, int64_t items_bound, int items_per_wg, 
     }
     if (K > 0 && grid >= K) grid = grid / K * K;
     return grid > 0 ? grid : 1;
+}
+
+// Workgroups per CU of a grid whose workgroups take their first tiles by rank, with `bytes` of LDS
+// each: LDS is given out in pieces of 1280 bytes, which the occupancy query leaves out, and the
+// tiles of a workgroup that is not resident start late (recognition of 16000 sequences under 12
+// models of 16 states with 300 symbols, 32192 bytes: 432 us on five per CU, 351 on the four that
+// fit; of 20000 under 12 of 32 states with 347 symbols: 1054 us on three, 974 on two).  Where
+// rounding the grid down to a multiple of K costs the smaller count 5 % more, the late ones are the
+// lesser evil (3000 sequences under 300 and 600 models of 16 states with 300 symbols: 258 and 537
+// us on five per CU, 274 and 685 on four).
+inline int ranked_per_cu(int per_cu, size_t bytes, int cus, int K) {
+    const int fit = std::max((int)(160 * 1024 / ((bytes + 1279) / 1280 * 1280)), 1);
+    if (per_cu <= fit) return std::max(per_cu, 1);
+    auto grid = [&](int n) { return (int64_t)(n * cus >= K ? n * cus / K * K : n * cus); };
+    return grid(per_cu) * fit * 20 > grid(fit) * per_cu * 21 ? per_cu : fit;
 }
 
 // Rank of workgroup i of a model's n in the model's list of tiles, longest first, when each
