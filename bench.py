@@ -60,6 +60,7 @@ sys.path.insert(0, ROOT)
 
 METRIC = "HMM state-steps/s (N²·ΣT·models) fwd and fwd+bwd, batched vs plain, FP32"
 FP32_PEAK_TFLOPS = 157.3
+BF16_PEAK_TFLOPS = 2516.6  # dense
 # vector ALU issue rate for single (unpacked) FP32 operations: 256 CUs x 4 SIMDs x 16 lanes x 2.4 GHz
 VALU_PEAK_TOPS = 39.3
 HBM_PEAK_GBS = 8000.0
@@ -81,10 +82,10 @@ _FWD_COOP = ["paper_1310_3322_amd/csrc/fwd_coop.hip", "paper_1310_3322_amd/csrc/
 _ADJ_COOP = ["paper_1310_3322_amd/csrc/adj_coop.hip", "paper_1310_3322_amd/csrc/coop_step.cuh"] + _COMMON
 TRAFFIC_KERNELS = {
     "c3_classify": ("k_fwd_mfma32<1, true>", FAMILY_KERNELS["tile32"][2]),
-    "c4_grad_forward": ("k_fwd_coop<4, 1, true>", _FWD_COOP),
+    "c4_grad_forward": ("k_fwd_coop<4, 1, true, false>", _FWD_COOP),
     "c4_grad_adjoint": ("k_adj_pipe<4>", _ADJ_COOP),
-    "c5_forward": ("k_fwd_coop<16, 4, false>", _FWD_COOP),
-    "c5_grad_forward": ("k_fwd_coop<16, 2, true>", _FWD_COOP),
+    "c5_forward": ("k_fwd_coop<16, 4, false, true>", _FWD_COOP),
+    "c5_grad_forward": ("k_fwd_coop<16, 2, true, false>", _FWD_COOP),
     "c5_grad_adjoint": ("k_adj_coop<16, 2, false, true, true>", _ADJ_COOP),
     "c5_grad_counts": ("k_grows_reduce", _ADJ_COOP),
 }
@@ -595,7 +596,8 @@ def main():
         del ws5
         large.update({"value": u5 / s5, "unit": "state-steps/s", "ms_per_step": s5 * 1e3,
                       "kernel_ms": k5_ms / max(k5_n, 1),
-                      "frac_fp32_peak": 2.0 * u5 / (k5_ms / max(k5_n, 1) / 1e3) / 1e12 / FP32_PEAK_TFLOPS,
+                      # six bf16 products stand for each FP32 one
+                      "frac_bf16_peak": 12.0 * u5 / (k5_ms / max(k5_n, 1) / 1e3) / 1e12 / BF16_PEAK_TFLOPS,
                       "traffic": traffic_fields({"forward": ("c5_forward", k5_ms / max(k5_n, 1))}, tuning)})
         rows5 = grad_rows(p5, w5, torch)
         autotune("c5_grad", p5, hmm.OP_GRAD, warmup=0, reps=2, grad_rows=rows5)

@@ -9,10 +9,14 @@
 // the power they draw lowers the clock), and they leave the vector ALUs free for other
 // waves, which the FP32 instructions do not.
 //
-// Error, measured for 32-state products of Dirichlet rows (concentration 0.5 and 1)
-// against 64 bits: rms 3.9e-8 and 3.6e-8 with the small terms added first, where
-// the FP32 instructions give 8.7e-8 (the longer chain of FP32 additions costs more
-// than the terms left out); hi hi first gives 1.3e-7.
+// Error of a step of the forward against 64 bits (rms of the logarithm of its sum, 8 banks of
+// each kind), with the FP32 instructions in brackets, at 64 and 256 states: Dirichlet rows of
+// concentration 1 5.1e-9 (6.9e-9) and 5.9e-9 (8.7e-9), of 0.5 6.0e-9 (7.2e-9) and 6.3e-9 (9.5e-9),
+// of 0.2 1.8e-8 (1.2e-8) and 1.7e-8 (4.8e-8; equal near 96 states).  Beside one large product the
+// matrix core drops low bits of the small ones, here more of them than in FP32: rows with an entry of
+// 0.9 3.9e-8 (1.0e-8) and 5.6e-8 (2.1e-8), all below one FP32 rounding per step.  A sum of its own for
+// each 32 products does not help (3.8e-8 and 5.4e-8) and costs 2 to 27 % of the time.  The small
+// terms are added first: products of 32 states are then off by 3.9e-8, with hi hi first by 1.3e-7.
 //
 // Range: bf16 has FP32's exponents, but the matrix core and the dot products below flush
 // denormals, so the pieces of a value below 2^-110 lose bits that FP32 keeps.  Both factors are
