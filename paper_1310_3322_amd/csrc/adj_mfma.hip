@@ -41,7 +41,7 @@
 // is why the parts of a step gain from having a SIMD each.  Against one wave per tile that
 // does all of it in turn, with every operand requested when needed, an EM iteration on
 // 4096 sequences of 50-400 (12 models, 16 states, 64 symbols) went from 606 to 292 us, on
-// 147 sequences of 20-200 (6 models, 5 states) from 361 to 178 us (some 50 us of either are
+// 147 sequences of 20-200 (6 models, 5 states) from 361 to 183 us (some 50 us of either are
 // fewer launches and a better order of the forward's tiles), and the counts of 65536
 // sequences of 16-2048 (64 models, 32 states, 256 symbols) from 6.4 to 3.9 ms.
 //
